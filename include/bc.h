@@ -170,7 +170,7 @@ typedef struct {
                              sources need */
     int32_t autotune;     /* 1 = time candidate settings once per graph and keep the best:
                              band width, workgroup size, dependency method, lane_max_deg,
-                             the expansion degree tiers and the sources in flight, each
+                             the degree tiers and the sources in flight, each
                              unless set here, on a prefix of the source list (batched
                              form); later calls reuse the choice (bc_get_graph_info) */
     int32_t accumulate;   /* 0 = default, 1 = per-slot partial sums + reduction,
@@ -181,9 +181,9 @@ typedef struct {
                              shortest-path DAG recorded by the count pass, band by band in
                              reverse and in Kahn's order inside a band, 2 = pull over
                              out-arcs band by band in reverse */
-    int32_t virtual_warp; /* frontier expansion: 0 = by degree, one lane per vertex up to 8
-                             arcs, a group of 16 lanes up to 64, a whole wave above (and in
-                             the batched form the whole workgroup above 512);
+    int32_t virtual_warp; /* frontier expansion: 0 = the arcs of up to 64 queued vertices
+                             spread evenly over a wave (and in the batched form a vertex
+                             of more than 512 arcs over the whole workgroup);
                              1, 2, 4, ..., 64 = a fixed group of that many lanes per vertex
                              (the warp-centric mapping of Sec. 3.4) */
     int32_t node_parallel;/* batched frontier expansion: 0 = over the queue (work-efficient,
@@ -198,13 +198,13 @@ typedef struct {
                              vertices below the window and values beyond it are kept in
                              device memory.  Suits graphs whose arc weights are about the
                              window's width or less */
-    /* Degree tiers of the adaptive frontier expansion (virtual_warp = 0; the
-       degree-aware thread mapping of Sec. 3.4 on 64-lane wavefronts).  A queued
-       vertex with d out-arcs is expanded by one lane if d <= expand_lane_deg, by a
-       group of 16 lanes if d <= wave_max_deg, else by one whole wave; in the
-       batched form a vertex with d > wg_min_deg is expanded by the whole
+    /* Degree tiers (the degree-aware thread mapping of Sec. 3.4 on 64-lane
+       wavefronts).  The adaptive frontier expansion (virtual_warp = 0) spreads
+       the arcs of a wave's queued vertices evenly over its lanes; in the batched
+       form a vertex with more than wg_min_deg out-arcs is expanded by the whole
        workgroup after the pass.  The count pass hands vertices with more than
-       wave_max_deg in-arcs to a whole wave.  0 = default (8, 64, 512); a
+       wave_max_deg in-arcs to a whole wave.  expand_lane_deg has no effect but
+       as the lower bound of wave_max_deg.  0 = default (8, 64, 512); a
        threshold below the one before it is raised to it.  The plain form has no
        workgroup tier; the interleaved form uses none of them. */
     int32_t expand_lane_deg;

@@ -2,10 +2,10 @@
 //
 // Coordinate descent, each candidate timed on a prefix of the caller's
 // source list: the near-far band width, the workgroup size, the dependency
-// method, the width of the LDS distance entries, the count pass's lane
-// threshold, the three degree thresholds of the frontier expansion (the
-// degree-aware thread mapping of Sec. 3.4, whose virtual warp width the paper
-// tunes per graph, Fig. 5) and the number of sources in flight.  The winner is cached on the graph handle and reused by
+// method, the width of the LDS distance entries, the count pass's lane and
+// wave thresholds, the expansion's workgroup threshold (the degree-aware
+// thread mapping of Sec. 3.4, whose virtual warp width the paper tunes per
+// graph, Fig. 5) and the number of sources in flight.  The winner is cached on the graph handle and reused by
 // later calls; fields the caller sets are never searched.
 #include <algorithm>
 #include <cstring>
@@ -140,17 +140,6 @@ void autotune(bc_graph *g, ResolvedOptions &r, const bc_options *opt, const int3
                     continue;
                 ResolvedOptions t = S.best;
                 t.lane_max = lm;
-                S.consider(t);
-            }
-        }
-        if (!o.expand_lane_deg) {
-            const int l0 = S.best.lane_deg;
-            for (int ld : {4, 16, 32}) {
-                if (ld == l0)
-                    continue;
-                ResolvedOptions t = S.best;
-                t.lane_deg = ld;
-                order_tiers(t);
                 S.consider(t);
             }
         }

@@ -752,9 +752,8 @@ void bucket_plan(const bc_graph *g, const ResolvedOptions &r, int &buckets, int 
               (r.far_buckets == 1 || (r.far_buckets == 0 && spans >= 16));
 }
 
-void set_tier_args(const bc_graph *g, int lane_deg, int wave_deg, int wg_deg, BatchArgs &a)
+void set_tier_args(const bc_graph *g, int wave_deg, int wg_deg, BatchArgs &a)
 {
-    a.lane_deg = (uint32_t)lane_deg;
     a.wave_deg = (uint32_t)wave_deg;
     a.wg_deg = (uint32_t)wg_deg;
     a.hubs = g->maxdeg > wg_deg;
@@ -792,7 +791,7 @@ void launch_batched_pass(bc_graph *g, const ResolvedOptions &r, const int32_t *s
     a.perm = g->perm_dev();
     a.H = r.lds_vertices;
     a.lds_bits = r.lds_bits;
-    set_tier_args(g, r.lane_deg, r.wave_deg, r.wg_deg, a);
+    set_tier_args(g, r.wave_deg, r.wg_deg, a);
     a.kahn = r.dep_mode == 1 ? 1 : 0;
     a.vw = r.vw;
     a.node_parallel = r.node_parallel;
@@ -870,7 +869,6 @@ static void run_plain(bc_graph *g, const ResolvedOptions &r, const int32_t *src_
     a.bc_out = nullptr; // the output travels in the control block
     a.delta = (uint32_t)r.delta;
     a.lane_max = r.lane_max;
-    a.lane_deg = (uint32_t)r.lane_deg;
     a.wave_deg = (uint32_t)r.wave_deg;
     DevCounters *c = (DevCounters *)g->ctl.p;
     a.stats = &c->stats;
@@ -891,7 +889,7 @@ static void run_plain(bc_graph *g, const ResolvedOptions &r, const int32_t *src_
     const int PLAIN_GRAPH_PAIRS = 32;
     if (!g->plain_exec || g->plain_exec_delta != a.delta || g->plain_exec_lane_max != a.lane_max ||
         g->plain_exec_vw != a.vw || g->plain_exec_slab != (const void *)a.slab_base ||
-        g->plain_exec_tiers != (((uint64_t)a.lane_deg << 32) | a.wave_deg)) {
+        g->plain_exec_tiers != a.wave_deg) {
         if (g->plain_exec) {
             (void)hipGraphExecDestroy(g->plain_exec);
             g->plain_exec = nullptr;
@@ -910,7 +908,7 @@ static void run_plain(bc_graph *g, const ResolvedOptions &r, const int32_t *src_
         g->plain_exec_lane_max = a.lane_max;
         g->plain_exec_vw = a.vw;
         g->plain_exec_slab = (const void *)a.slab_base;
-        g->plain_exec_tiers = ((uint64_t)a.lane_deg << 32) | a.wave_deg;
+        g->plain_exec_tiers = a.wave_deg;
     }
     const unsigned long long iter_cap = 8ull * (unsigned long long)g->n + 1024ull;
     hipEvent_t e0, e1;

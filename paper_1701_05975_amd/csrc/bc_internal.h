@@ -81,9 +81,9 @@ struct ResolvedOptions {
     int lds_bits = 32;    // width of an LDS distance entry (8, 16 or 32)
     int dep_mode = 1;     // 1 recorded DAG (Kahn), 2 band pulls
     int vw = 0;           // expansion lanes per vertex (0 adaptive)
-    int lane_deg = BC_DEF_LANE_DEG; // adaptive expansion: one lane up to this many arcs,
-    int wave_deg = BC_DEF_WAVE_DEG; // a group of lanes up to this many, a wave above,
-    int wg_deg = BC_HUB_DEG;        // the whole workgroup above this (batched form)
+    int lane_deg = BC_DEF_LANE_DEG; // lower bound of wave_deg (reported only)
+    int wave_deg = BC_DEF_WAVE_DEG; // count pass: a wave above this many in-arcs
+    int wg_deg = BC_HUB_DEG;        // expansion: the whole workgroup above this (batched form)
     int node_parallel = 0;
     int far_buckets = 0;  // batched: 0 auto, 1 far-bucket ring, 2 two-tier pile
     int il_groups = 0;    // interleaved form: groups of 64 sources per sweep (0 = by memory)
@@ -134,7 +134,7 @@ struct bc_graph {
     uint32_t plain_exec_delta = 0;
     int plain_exec_lane_max = 0;
     int plain_exec_vw = 0;
-    uint64_t plain_exec_tiers = 0;
+    uint32_t plain_exec_tiers = 0;
     const void *plain_exec_slab = nullptr;
 
     Workspace batched, plain;
@@ -188,7 +188,7 @@ void set_inarc_bound(bc_graph *g, hipStream_t st);
 // used, and its number of buckets.
 void bucket_plan(const bc_graph *g, const ResolvedOptions &r, int &buckets, int &nbk);
 // Degree-tier fields of the batched kernel's arguments.
-void set_tier_args(const bc_graph *g, int lane_deg, int wave_deg, int wg_deg, BatchArgs &a);
+void set_tier_args(const bc_graph *g, int wave_deg, int wg_deg, BatchArgs &a);
 void read_device_counters(bc_graph *g, hipStream_t st, DevCounters &out);
 // Status of a finished computation from its device counters (throws on an
 // out-of-range source, a tripped iteration bound or a count overflow).

@@ -222,6 +222,41 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x)
     return x;
 }
 
+// Inclusive prefix sums over the lanes, and the OR of all lanes (uniform), by
+// DPP row shifts and row broadcasts.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false);
+}
+
+__device__ __forceinline__ uint32_t wave_incl_sum_u32(uint32_t x)
+{
+    x += dpp_or_zero<0x111, 0xf>(x); // row_shr:1
+    x += dpp_or_zero<0x112, 0xf>(x);
+    x += dpp_or_zero<0x114, 0xf>(x);
+    x += dpp_or_zero<0x118, 0xf>(x);
+    x += dpp_or_zero<0x142, 0xa>(x); // row_bcast:15
+    x += dpp_or_zero<0x143, 0xc>(x); // row_bcast:31
+    return x;
+}
+
+__device__ __forceinline__ uint32_t wave_or_u32(uint32_t x)
+{
+    x |= dpp_or_zero<0x111, 0xf>(x);
+    x |= dpp_or_zero<0x112, 0xf>(x);
+    x |= dpp_or_zero<0x114, 0xf>(x);
+    x |= dpp_or_zero<0x118, 0xf>(x);
+    x |= dpp_or_zero<0x142, 0xa>(x);
+    x |= dpp_or_zero<0x143, 0xc>(x);
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, WAVE - 1);
+}
+
+__device__ __forceinline__ uint64_t wave_or_u64(uint64_t x)
+{
+    return (uint64_t)wave_or_u32((uint32_t)(x >> 32)) << 32 | wave_or_u32((uint32_t)x);
+}
+
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x)
 {
     for (int o = 32; o > 0; o >>= 1)

@@ -29,7 +29,7 @@ struct BatchArgs {
     const uint32_t *emap;         // in-row position -> caller arc index
     uint32_t delta;               // band width
     int lane_max;                 // count/dependency passes: lane up to this many arcs
-    uint32_t lane_deg, wave_deg;  // expansion tiers: lane / group of lanes / wave by degree
+    uint32_t wave_deg;            // count pass: more in-arcs than this -> the whole wave
     uint32_t wg_deg;              // expansion: more arcs than this -> the whole workgroup
     DevStats *stats;
     unsigned long long *err;      // [0] error bits, [1] first overflowing source index
@@ -64,7 +64,7 @@ struct PlainArgs {
     double *bc_out;
     uint32_t delta;
     int lane_max;
-    uint32_t lane_deg, wave_deg;  // expansion tiers, as in BatchArgs
+    uint32_t wave_deg;            // as in BatchArgs
     DevStats *stats;
     unsigned long long *err;
 };

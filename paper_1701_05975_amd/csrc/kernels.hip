@@ -324,7 +324,7 @@ __device__ __forceinline__ void lds8_rebase(const Slab &S, uint32_t nb, int tid,
 }
 
 template <bool PACKED, int NT, bool ATOMIC_BC, int LB, bool BKT>
-__global__ __launch_bounds__(NT) void k_batched(BatchArgs a)
+__global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
 {
     __shared__ WgCtl C;
     extern __shared__ uint32_t lds_dist[];
@@ -476,7 +476,6 @@ __global__ __launch_bounds__(NT) void k_batched(BatchArgs a)
                 ec.thr = C.thr;
                 ec.tag_next = C.gen + 1;
                 ec.band_gen = C.band_gen;
-                ec.lane_max = a.lane_max;
                 ec.next_q = C.cur ? S.qa : S.qb;
                 ec.next_cnt = &C.next_cnt;
                 ec.order = S.order;
@@ -491,8 +490,6 @@ __global__ __launch_bounds__(NT) void k_batched(BatchArgs a)
                 ec.huge_cnt = &C.huge_cnt;
                 ec.keys = a.ebc == nullptr;
                 ec.trow = g.trow;
-                ec.lane_deg = a.lane_deg;
-                ec.wave_deg = a.wave_deg;
                 ec.wg_deg = a.wg_deg;
                 ec.bk = S.fa;
                 ec.bcnt = C.bcnt;
@@ -501,23 +498,16 @@ __global__ __launch_bounds__(NT) void k_batched(BatchArgs a)
                 ec.bcap = a.bcap;
                 ec.forced = &C.forced;
                 uint32_t fmin = BC_INF, omin = BC_INF;
-                expand_pass<PACKED, WG_SCOPE, BKT>(g, S, ec, fmin, omin, st_imp);
-                if (hubs) {
-                    __syncthreads();
-                    // the listed hubs, each by the whole workgroup
-                    const int nh = C.huge_cnt < EXPAND_WG_CAP ? C.huge_cnt : EXPAND_WG_CAP;
-                    for (int h = 0; h < nh; ++h) {
-                        const int32_t v = C.huge_q[h];
-                        const uint32_t hb = g.row[v], he = g.row[v + 1];
-                        const uint32_t hd = dist_get(S, v);
-                        for (uint32_t e = hb + tid; e < he; e += NT) {
-                            uint32_t u, w;
-                            arc_at<PACKED>(g.arc, g.wt, e, g.wshift, g.wmask, u, w);
-                            relax<WG_SCOPE, BKT>(S, ec, u, hd + w, dist_peek(S, u), (uint32_t)v, fmin,
-                                            omin, st_imp);
-                        }
-                    }
+                CandBuf cb{0u, 0u, 0u, 0};
+#pragma nounroll
+                for (int part = 0;; ++part) {
+                    expand_pass<PACKED, WG_SCOPE, BKT>(g, S, ec, part == 1, cb, fmin, omin,
+                                                       st_imp);
+                    if (!hubs || part == 1)
+                        break;
+                    __syncthreads(); // the hubs the pass listed, each by the whole workgroup
                 }
+                cand_flush<WG_SCOPE, BKT>(S, ec, cb, fmin, omin, st_imp);
                 fmin = wave_min_u32(fmin);
                 omin = wave_min_u32(omin);
                 if (lane == 0 && fmin != BC_INF)
@@ -957,7 +947,6 @@ __global__ __launch_bounds__(256) void k_plain_step(PlainArgs a)
         ec.thr = c->thr;
         ec.tag_next = c->gen + 1;
         ec.band_gen = c->band_gen;
-        ec.lane_max = a.lane_max;
         ec.next_q = c->cur ? S.qa : S.qb;
         ec.next_cnt = &c->next_cnt;
         ec.order = S.order;
@@ -972,12 +961,12 @@ __global__ __launch_bounds__(256) void k_plain_step(PlainArgs a)
         ec.huge_cnt = nullptr;
         ec.keys = 0;
         ec.trow = nullptr;
-        ec.lane_deg = a.lane_deg;
-        ec.wave_deg = a.wave_deg;
         ec.wg_deg = BC_INF;
         uint32_t fmin = BC_INF, omin = BC_INF;
         uint64_t imp = 0;
-        expand_pass<PACKED, AG_SCOPE>(g, S, ec, fmin, omin, imp);
+        CandBuf cb{0u, 0u, 0u, 0};
+        expand_pass<PACKED, AG_SCOPE>(g, S, ec, false, cb, fmin, omin, imp);
+        cand_flush<AG_SCOPE, false>(S, ec, cb, fmin, omin, imp);
         fmin = wave_min_u32(fmin);
         unsigned long long x = imp;
         for (int o = 32; o > 0; o >>= 1)

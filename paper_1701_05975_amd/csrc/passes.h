@@ -3,14 +3,14 @@
 // waves of one workgroup and counters in LDS; the plain form with every wave
 // of the grid and counters in global memory.
 //
-// Mapping of vertices to lanes (the warp-centric idea of Sec. 3.4 recast for
-// 64-lane wavefronts), by degree: a low-degree vertex is handled by one lane,
-// which walks its arcs in order; a medium one by a group of EXPAND_GROUP
-// lanes; a large one by the whole wave, the 64 lanes striding over its arcs
-// together (and in the batched expansion a hub by the whole workgroup).  Only
-// queued vertices get lanes (the work-efficient queue of Sec. 3.3); a fixed
-// group width and a scan over every vertex (node-parallel) are selectable for
-// comparison.
+// Mapping of work to lanes (the warp-centric idea of Sec. 3.4 recast for
+// 64-lane wavefronts): the expansion lays the arcs of up to 64 queued vertices
+// out flat over the wave, so that every lane has an arc whatever the degrees
+// are, and a hub's arcs over the whole workgroup; the count pass handles a
+// vertex by one lane, a group of EXPAND_GROUP lanes or the whole wave by its
+// in-degree.  Only queued vertices get lanes (the work-efficient queue of
+// Sec. 3.3); a fixed group width and a scan over every vertex (node-parallel)
+// are selectable for comparison.
 #pragma once
 
 #include "dev_common.h"
@@ -149,7 +149,6 @@ struct ExpandCtx {
     uint32_t thr;         // band threshold: d < thr is near
     int32_t tag_next;     // tag of the queue being filled
     int32_t band_gen;     // tag of the band's first queue
-    int lane_max;
     int32_t *next_q;
     int *next_cnt;
     int32_t *order;
@@ -163,9 +162,7 @@ struct ExpandCtx {
     int *huge_cnt;        // here for the whole workgroup to expand after the pass
     int keys;             // record each vertex's (distance, predecessor) key and ties
     const uint32_t *trow; // with keys: in-row offsets, whose slices hold the tie entries
-    uint32_t lane_deg;    // adaptive mapping: at most this many arcs -> one lane,
-    uint32_t wave_deg;    // at most this many -> a group of EXPAND_GROUP lanes, more -> a wave,
-    uint32_t wg_deg;      // more than this (batched, huge_q set) -> the whole workgroup
+    uint32_t wg_deg;      // more arcs than this (batched, huge_q set): the whole workgroup
     // Far-bucket ring (batched form, relax<.., true>; else the two-tier pile above).  A far
     // value below `bound` goes to bucket value / bdelta, slot bucket % nbk,
     // when that bucket is lower than any the vertex was put in before (its
@@ -220,29 +217,27 @@ __device__ __forceinline__ uint64_t *key_ptr(const Slab &S, int32_t v)
 #define LANE_UNROLL 2
 #endif
 
-// Adaptive expansion (Sec. 3.4's degree-aware mapping, three tiers): a vertex
-// with at most lane_deg arcs is walked by one lane, one with at most wave_deg
-// by a group of EXPAND_GROUP lanes, a larger one by the wave.  The thresholds
-// are run-time values (BC_DEF_LANE_DEG and BC_DEF_WAVE_DEG by default); the
-// group width is fixed.
+// Lanes of a group that counts one vertex of medium in-degree.
 #ifndef EXPAND_GROUP
 #define EXPAND_GROUP 16
 #endif
-// Fourth tier (batched form): a vertex with more than wg_deg arcs (default
-// BC_HUB_DEG) is expanded by every thread of the workgroup after the pass, so
-// that one hub does not keep one wave busy while the others wait at the
-// barrier.  The list holds EXPAND_WG_CAP vertices; further ones take the wave
-// path.
+// Hubs (batched form): a vertex with more than wg_deg arcs (default
+// BC_HUB_DEG) is expanded by every wave of the workgroup after the pass, so
+// that it does not keep one wave busy while the others wait at the barrier.
+// The list holds EXPAND_WG_CAP vertices; further ones stay with their wave.
 #define EXPAND_WG_CAP 256
 
+// Offers nd to u from tail (lanes with `cand`); every lane of the wave may
+// call it, active lanes together.
 template <int SCOPE, bool BKT = false>
-__device__ __forceinline__ void relax(const Slab &S, const ExpandCtx &c, uint32_t u, uint32_t nd,
-                                      uint32_t du, uint32_t tail, uint32_t &far_min,
-                                      uint32_t &outer_min, uint64_t &nimp)
+__device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, bool cand,
+                                             uint32_t u, uint32_t nd, uint32_t tail,
+                                             uint32_t &far_min, uint32_t &outer_min,
+                                             uint64_t &nimp)
 {
-    bool imp = false, tie = nd == du;
-    if (nd < du) {
-        uint32_t old = dist_min<SCOPE>(S, u, nd);
+    bool imp = false, tie = false;
+    if (cand) {
+        const uint32_t old = dist_min<SCOPE>(S, u, nd);
         imp = nd < old;
         tie = nd == old;
     }
@@ -319,6 +314,12 @@ __device__ __forceinline__ void relax(const Slab &S, const ExpandCtx &c, uint32_
     }
 }
 
+// Steps of 64 arcs whose loads are in flight together (1 to 4 measure within
+// 2% of each other on every workload: the commits bound the pass).
+#ifndef EXPAND_UNROLL
+#define EXPAND_UNROLL 2
+#endif
+
 // Fixed virtual-warp mapping (Sec. 3.4): a group of vw lanes per vertex,
 // striding over its arcs; vw = 1 is one thread per vertex, vw = 64 one wave.
 template <bool PACKED, int SCOPE, bool BKT = false>
@@ -347,29 +348,107 @@ __device__ __forceinline__ void expand_pass_vw(const DevGraph &g, const Slab &S,
         for (uint32_t e = beg + sub; e < end; e += W) {
             uint32_t u, w;
             arc_at<PACKED>(g.arc, g.wt, e, g.wshift, g.wmask, u, w);
-            relax<SCOPE, BKT>(S, c, u, dv + w, dist_peek(S, u), (uint32_t)v, far_min, outer_min, nimp);
+            relax_commit<SCOPE, BKT>(S, c, dv + w <= dist_peek(S, u), u, dv + w, (uint32_t)v, far_min,
+                                     outer_min, nimp);
         }
     }
 }
 
+// Candidates of one wave: offers that the pre-check found no worse than the
+// head's distance, held in registers, lane i holding the i-th, until 64 of
+// them can be committed together.  Only one arc in ten (Barabasi-Albert,
+// n = 100,000) to thirteen (R-MAT scale 20) improves its head, but nearly
+// every step of 64 arcs holds one, and a commit is a chain of an LDS or
+// global atomic, a returning tag atomic and queue appends: committing each
+// step's few cost that chain for every step.  Collected, a wave commits once
+// per 64 candidates.  With the flat arcs (the tiers by degree left half of
+// the lanes without an arc on those graphs): Barabasi-Albert, 4096 sources,
+// 196 -> 169 ms; R-MAT scale 20, 1024 sources, 400 -> 326 ms; Kronecker scale
+// 16, 256 sources, 27.4 -> 18.9 ms.
+struct CandBuf {
+    uint32_t u, nd, tail;
+    int cnt; // uniform
+};
+
+// Adds the lanes' candidates (called by the whole wave).  The permutation
+// sends candidates to the next free lanes and the other lanes to the rest.
+template <int SCOPE, bool BKT>
+__device__ __forceinline__ void cand_add(const Slab &S, const ExpandCtx &c, CandBuf &b, bool cand,
+                                         uint32_t u, uint32_t nd, uint32_t tail, uint32_t &far_min,
+                                         uint32_t &outer_min, uint64_t &nimp)
+{
+    const uint64_t mask = __ballot(cand);
+    if (mask == 0)
+        return;
+    const int lane = lane_id();
+    const int p = __popcll(mask);
+    const int below = (int)lanes_below(mask);
+    const int dst = ((b.cnt + (cand ? below : p + lane - below)) & (WAVE - 1)) << 2;
+    const uint32_t ru = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)u);
+    const uint32_t rnd = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)nd);
+    const uint32_t rt = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)tail);
+    const bool fresh = ((lane - b.cnt) & (WAVE - 1)) < p; // received a candidate
+    if (b.cnt + p < WAVE) {
+        if (fresh) {
+            b.u = ru;
+            b.nd = rnd;
+            b.tail = rt;
+        }
+        b.cnt += p;
+        return;
+    }
+    const bool low = lane < b.cnt;
+    relax_commit<SCOPE, BKT>(S, c, true, low ? b.u : ru, low ? b.nd : rnd, low ? b.tail : rt,
+                             far_min, outer_min, nimp);
+    b.cnt += p - WAVE;
+    b.u = ru;
+    b.nd = rnd;
+    b.tail = rt;
+}
+
+template <int SCOPE, bool BKT>
+__device__ __forceinline__ void cand_flush(const Slab &S, const ExpandCtx &c, CandBuf &b,
+                                           uint32_t &far_min, uint32_t &outer_min, uint64_t &nimp)
+{
+    if (b.cnt > 0)
+        relax_commit<SCOPE, BKT>(S, c, lane_id() < b.cnt, b.u, b.nd, b.tail, far_min, outer_min,
+                                 nimp);
+    b.cnt = 0;
+}
+
+// Expansion with the arcs of up to 64 queued vertices laid out flat over the
+// lanes (the degree-aware mapping of Sec. 3.4 carried to single arcs: every
+// lane has an arc whatever the degrees are).  `hubs`: the vertices listed in
+// huge_q instead of the queue, each by every wave together.  Called by whole
+// waves; candidates stay in b until cand_flush.
 template <bool PACKED, int SCOPE, bool BKT = false>
 __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, const ExpandCtx &c,
-                            uint32_t &far_min, uint32_t &outer_min, uint64_t &nimp)
+                                            bool hubs, CandBuf &b, uint32_t &far_min,
+                                            uint32_t &outer_min, uint64_t &nimp)
 {
     if (c.vw > 0) {
         expand_pass_vw<PACKED, SCOPE, BKT>(g, S, c, far_min, outer_min, nimp);
         return;
     }
     const int lane = lane_id();
-    const int len = c.all_vertices ? g.n : c.len;
-    for (int base = c.worker * WAVE; base < len; base += c.nworkers * WAVE) {
+    const int len = hubs                       ? (*c.huge_cnt < EXPAND_WG_CAP ? *c.huge_cnt
+                                                                              : EXPAND_WG_CAP)
+                    : c.all_vertices ? g.n
+                                     : c.len;
+    // a short queue is spread over every wave
+    int chunk = (len + c.nworkers - 1) / c.nworkers;
+    chunk = hubs ? 1 : chunk < WAVE ? chunk : WAVE;
+    const int first = hubs ? 0 : c.worker * chunk, stride = hubs ? 1 : c.nworkers * chunk;
+    const uint32_t p_first = hubs ? (uint32_t)c.worker * (WAVE * EXPAND_UNROLL) : 0u;
+    const uint32_t p_stride = (hubs ? (uint32_t)c.nworkers : 1u) * (WAVE * EXPAND_UNROLL);
+    for (int base = first; base < len; base += stride) {
         const int i = base + lane;
-        bool valid = i < len;
-        uint32_t beg = 0, end = 0, dv = BC_INF;
+        bool valid = lane < chunk && i < len;
+        uint32_t beg = 0, end = 0, dv = 0;
         int v = 0;
         if (valid) {
-            v = c.all_vertices ? i : c.items[i];
-            if (c.all_vertices)
+            v = hubs ? c.huge_q[i] : c.all_vertices ? i : c.items[i];
+            if (c.all_vertices && !hubs)
                 valid = S.stamp[v] == c.cur_tag;
             if (valid) {
                 beg = g.row[v];
@@ -377,87 +456,68 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
                 dv = dist_get(S, v);
             }
         }
-        const uint32_t deg = end - beg;
-        const bool light = valid && deg <= c.lane_deg;
-        const bool mid = valid && deg > c.lane_deg && deg <= c.wave_deg;
-        bool heavy = valid && deg > c.wave_deg;
-        if (c.huge_q) {
-            const bool huge = heavy && deg > c.wg_deg;
+        uint32_t deg = end - beg;
+        if (c.huge_q && !hubs) {
+            const bool huge = deg > c.wg_deg;
             const int k = wave_alloc(c.huge_cnt, huge);
             if (huge && k < EXPAND_WG_CAP) {
                 c.huge_q[k] = v;
-                heavy = false;
+                deg = 0;
             }
         }
-        if (light) {
-            for (uint32_t e0 = beg; e0 < end; e0 += LANE_UNROLL) {
-                uint32_t u[LANE_UNROLL], w[LANE_UNROLL], du[LANE_UNROLL];
+        // vertices with arcs to the first lanes, in order
+        const uint64_t has = __ballot(deg > 0);
+        const int items = __popcll(has);
+        if (has & (has + 1)) {
+            const int below = (int)lanes_below(has);
+            const int dst = (deg > 0 ? below : items + lane - below) << 2;
+            v = __builtin_amdgcn_ds_permute(dst, v);
+            beg = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)beg);
+            dv = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)dv);
+            deg = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)deg);
+        }
+        const uint32_t incl = wave_incl_sum_u32(deg);
+        const uint32_t off = incl - deg; // strictly increasing over the items
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+        const uint32_t shift = beg - off; // arc position of flat position p: p + shift
+        for (uint32_t p0 = p_first; p0 < total; p0 += p_stride) {
+            uint32_t u[EXPAND_UNROLL], nd[EXPAND_UNROLL], tl[EXPAND_UNROLL];
+            bool ok[EXPAND_UNROLL];
 #pragma unroll
-                for (int j = 0; j < LANE_UNROLL; ++j) {
-                    u[j] = 0;
-                    w[j] = 0;
-                    if (e0 + j < end)
-                        arc_at<PACKED>(g.arc, g.wt, e0 + j, g.wshift, g.wmask, u[j], w[j]);
+            for (int j = 0; j < EXPAND_UNROLL; ++j) {
+                const uint32_t q0 = p0 + WAVE * j, p = q0 + lane;
+                // the item whose arcs hold flat position p: the last one starting at
+                // or before it
+                const uint64_t starts = wave_or_u64(
+                    lane < items && off >= q0 && off - q0 < WAVE ? 1ull << (off - q0) : 0ull);
+                const int before = __popcll(__ballot(lane < items && off < q0));
+                const int it = before + (int)lanes_below(starts) + (int)((starts >> lane) & 1) - 1;
+                const uint32_t sh = (uint32_t)__shfl((int)shift, it);
+                const uint32_t d = (uint32_t)__shfl((int)dv, it);
+                tl[j] = (uint32_t)__shfl(v, it);
+                ok[j] = p < total;
+                u[j] = 0;
+                nd[j] = 0;
+                if (ok[j]) {
+                    uint32_t w;
+                    arc_at<PACKED>(g.arc, g.wt, p + sh, g.wshift, g.wmask, u[j], w);
+                    nd[j] = d + w;
                 }
-#pragma unroll
-                for (int j = 0; j < LANE_UNROLL; ++j)
-                    du[j] = e0 + j < end ? dist_peek(S, u[j]) : 0u;
-#pragma unroll
-                for (int j = 0; j < LANE_UNROLL; ++j)
-                    if (e0 + j < end)
-                        relax<SCOPE, BKT>(S, c, u[j], dv + w[j], du[j], (uint32_t)v, far_min, outer_min,
-                                     nimp);
             }
-        }
-        // Medium degree: up to WAVE / EXPAND_GROUP vertices at a time, one per
-        // group of lanes.  The shuffles run on every lane: a lane whose group
-        // has no vertex may be the source another group reads from.
-        uint64_t mm = __ballot(mid);
-        const int grp = lane / EXPAND_GROUP, sub = lane % EXPAND_GROUP;
-        while (mm) {
-            uint64_t t = mm;
-            for (int k = 0; k < grp; ++k)
-                t &= t - 1;
-            const bool have = t != 0;
-            const int l = have ? __ffsll((unsigned long long)t) - 1 : 0;
-            for (int k = 0; k < WAVE / EXPAND_GROUP; ++k)
-                mm &= mm - 1;
-            const uint32_t mb = (uint32_t)__shfl((int)beg, l);
-            const uint32_t me0 = (uint32_t)__shfl((int)end, l);
-            const uint32_t md = (uint32_t)__shfl((int)dv, l);
-            const uint32_t mv = (uint32_t)__shfl(v, l);
-            const uint32_t me = have ? me0 : mb;
-            constexpr int G = EXPAND_GROUP;
-            for (uint32_t e0 = mb + sub; e0 < me; e0 += G * 2) {
-                uint32_t u[2], w[2], du[2];
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    u[j] = 0;
-                    w[j] = 0;
-                    if (e0 + G * j < me)
-                        arc_at<PACKED>(g.arc, g.wt, e0 + G * j, g.wshift, g.wmask, u[j], w[j]);
+            for (int j = 0; j < EXPAND_UNROLL; ++j)
+                ok[j] = ok[j] && nd[j] <= dist_peek(S, u[j]);
+            // one copy of the commit code for every j
+#pragma nounroll
+            for (int j = 0; j < EXPAND_UNROLL; ++j) {
+                cand_add<SCOPE, BKT>(S, c, b, ok[0], u[0], nd[0], tl[0], far_min, outer_min, nimp);
+#pragma unroll
+                for (int i = 0; i + 1 < EXPAND_UNROLL; ++i) {
+                    ok[i] = ok[i + 1];
+                    u[i] = u[i + 1];
+                    nd[i] = nd[i + 1];
+                    tl[i] = tl[i + 1];
                 }
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    du[j] = e0 + G * j < me ? dist_peek(S, u[j]) : 0u;
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    if (e0 + G * j < me)
-                        relax<SCOPE, BKT>(S, c, u[j], md + w[j], du[j], mv, far_min, outer_min, nimp);
-            }
-        }
-        uint64_t hm = __ballot(heavy);
-        while (hm) {
-            const int l = __ffsll((unsigned long long)hm) - 1;
-            hm &= hm - 1;
-            const uint32_t hb = (uint32_t)__shfl((int)beg, l);
-            const uint32_t he = (uint32_t)__shfl((int)end, l);
-            const uint32_t hd = (uint32_t)__shfl((int)dv, l);
-            const uint32_t hv = (uint32_t)__shfl(v, l);
-            for (uint32_t e = hb + lane; e < he; e += WAVE) {
-                uint32_t u, w;
-                arc_at<PACKED>(g.arc, g.wt, e, g.wshift, g.wmask, u, w);
-                relax<SCOPE, BKT>(S, c, u, hd + w, dist_peek(S, u), hv, far_min, outer_min, nimp);
             }
         }
     }

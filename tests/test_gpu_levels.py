@@ -1,0 +1,58 @@
+"""The batched form's flat expansion, candidate batches and level passes at the
+edges of their tiles: queue lengths and degrees around the wavefront width and
+the workgroup's waves, vertices without out-arcs between others, hubs, and ties
+in every position of the recorded predecessor lists."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1701_05975_amd import bc, graphgen as gg
+
+pytestmark = pytest.mark.gpu
+
+
+def layered(width: int, degrees, seed: int):
+    """Source 0 -> `width` queued vertices of the given degrees (cycled; 0
+    included) -> a pool of heads that lead back into one vertex; small weights,
+    so heads are offered equal, better and worse distances."""
+    rng = np.random.default_rng(seed)
+    deg = np.resize(np.asarray(degrees), width)
+    pool = max(int(deg.max()), 70) + 7
+    n = 1 + width + pool + 1
+    src = [np.zeros(width, np.int64)]
+    dst = [1 + np.arange(width)]
+    for i, d in enumerate(deg):
+        src.append(np.full(d, 1 + i))
+        dst.append(1 + width + rng.choice(pool, size=d, replace=False))
+    src.append(1 + width + np.arange(pool))
+    dst.append(np.full(pool, n - 1))
+    src, dst = np.concatenate(src), np.concatenate(dst)
+    return gg.csr_from_arcs(n, src, dst, rng.integers(1, 4, size=src.shape[0]), directed=True)
+
+
+@pytest.mark.parametrize("width", [1, 15, 16, 17, 63, 64, 65, 1023, 1025, 2049])
+@pytest.mark.parametrize("degrees", [[1], [0, 3], [63, 64, 65], [0, 0, 127, 1, 129], [2, 700, 5]],
+                         ids=str)
+def test_layers(width, degrees):
+    if width > 1100 and max(degrees) > 200:
+        pytest.skip("covered by the smaller widths")
+    g = layered(width, degrees, seed=width + len(degrees))
+    srcs = np.concatenate([np.zeros(3, np.int64), np.arange(0, g.n, max(1, g.n // 40))])
+    want = oracle.oracle_bc(g, srcs)
+    G = bc.Graph(g)
+    for opts in (dict(), dict(wg_threads=1024, delta=1), dict(delta=1, far_buckets=1),
+                 dict(lane_max_deg=1, wg_min_deg=64), dict(accumulate=2), dict(dep_mode=2),
+                 dict(keep=1)):
+        H = bc.Graph(g, keep_order=True) if opts.pop("keep", 0) else G
+        got, st = H.bc(srcs, **opts)
+        # sums of at most a few thousand non-negative terms: 1e-16 relative each
+        assert np.all(got[want == 0] == 0)
+        nz = want != 0
+        assert nz.sum() == 0 or np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11, opts
+        d, sg, _ = H.source_state(0, **opts)
+        od, osg, _, _ = oracle.oracle_source_state(g, 0)
+        od = np.where(od == np.iinfo(np.int64).max, 2**31 - 1, od)
+        assert np.array_equal(d, od) and np.array_equal(sg, osg), opts
+    G.close()
