@@ -162,9 +162,9 @@ typedef struct {
                              interleaved: at most this many sources per sweep */
     int32_t delta;        /* near-far band width in weight units (>= 1); 0 = heuristic (the
                              interleaved form: at least 4 times the maximum weight) */
-    int32_t lane_max_deg; /* count and dependency passes: vertices with at most this many
-                             in-arcs (recorded predecessors) are handled by one lane, larger
-                             ones by a whole 64-lane wave */
+    int32_t lane_max_deg; /* count pass: at most this many recorded predecessors are summed
+                             by one lane, more by a whole 64-lane wave (plain form: in-arcs,
+                             and out-arcs in the dependency pass) */
     int32_t wg_threads;   /* batched: threads per workgroup (256, 512 or 1024); with batch
                              set, a CU's LDS is shared only by the workgroups those
                              sources need */
@@ -177,10 +177,9 @@ typedef struct {
                              2 = device-wide FP64 atomic adds into the output */
     int32_t lds_vertices; /* batched: distances of this many highest in-degree vertices are
                              kept in LDS per source; 0 = as many as fit, -1 = none */
-    int32_t dep_mode;     /* batched dependency pass: 0 = default (1), 1 = push along the
-                             shortest-path DAG recorded by the count pass, band by band in
-                             reverse and in Kahn's order inside a band, 2 = pull over
-                             out-arcs band by band in reverse */
+    int32_t dep_mode;     /* batched dependency pass, over the levels of the shortest-path
+                             DAG in reverse: 0 = default (1), 1 = push along the DAG
+                             recorded by the count pass, 2 = pull over out-arcs */
     int32_t virtual_warp; /* frontier expansion: 0 = the arcs of up to 64 queued vertices
                              spread evenly over a wave (and in the batched form a vertex
                              of more than 512 arcs over the whole workgroup);
@@ -202,8 +201,8 @@ typedef struct {
        wavefronts).  The adaptive frontier expansion (virtual_warp = 0) spreads
        the arcs of a wave's queued vertices evenly over its lanes; in the batched
        form a vertex with more than wg_min_deg out-arcs is expanded by the whole
-       workgroup after the pass.  The count pass hands vertices with more than
-       wave_max_deg in-arcs to a whole wave.  expand_lane_deg has no effect but
+       workgroup after the pass.  The plain form's count pass hands vertices with
+       more than wave_max_deg in-arcs to a whole wave.  expand_lane_deg has no effect but
        as the lower bound of wave_max_deg.  0 = default (8, 64, 512); a
        threshold below the one before it is raised to it.  The plain form has no
        workgroup tier; the interleaved form uses none of them. */

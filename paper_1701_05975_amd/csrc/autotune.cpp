@@ -2,8 +2,8 @@
 //
 // Coordinate descent, each candidate timed on a prefix of the caller's
 // source list: the near-far band width, the workgroup size, the dependency
-// method, the width of the LDS distance entries, the count pass's lane and
-// wave thresholds, the expansion's workgroup threshold (the degree-aware
+// method, the width of the LDS distance entries, the count pass's lane
+// threshold, the expansion's workgroup threshold (the degree-aware
 // thread mapping of Sec. 3.4, whose virtual warp width the paper tunes per
 // graph, Fig. 5) and the number of sources in flight.  The winner is cached on the graph handle and reused by
 // later calls; fields the caller sets are never searched.
@@ -140,17 +140,6 @@ void autotune(bc_graph *g, ResolvedOptions &r, const bc_options *opt, const int3
                     continue;
                 ResolvedOptions t = S.best;
                 t.lane_max = lm;
-                S.consider(t);
-            }
-        }
-        if (!o.wave_max_deg) {
-            const int w0 = S.best.wave_deg;
-            for (int wd : {32, 128, 256}) {
-                if (wd == w0 || wd < S.best.lane_deg)
-                    continue;
-                ResolvedOptions t = S.best;
-                t.wave_deg = wd;
-                order_tiers(t);
                 S.consider(t);
             }
         }

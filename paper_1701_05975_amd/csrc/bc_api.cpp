@@ -744,17 +744,15 @@ void bucket_plan(const bc_graph *g, const ResolvedOptions &r, int &buckets, int 
     // weights span many bands, where the pile would be rescanned many times.
     const int64_t spans = ((int64_t)g->wmax + r.delta - 1) / std::max(r.delta, 1);
     nbk = (int)std::min<int64_t>(spans + 2, BC_BUCKETS_MAX);
-    // bucket keys (BUCKET_KEY) stay below the count pass's predecessor
-    // encodings only while vertex ids and bucket indices stay below 2^30
+    // bucket indices are 32-bit, with room for the ring's width beyond the last
     const int64_t last_bucket = (int64_t)std::max(g->n - 1, 0) * g->wmax / std::max(r.delta, 1);
-    const bool keys_fit = g->n < (1 << 30) && last_bucket < (int64_t)1 << 30;
-    buckets = g->packed && keys_fit &&
+    const bool index_fits = g->n < (1 << 30) && last_bucket < (int64_t)1 << 30;
+    buckets = g->packed && index_fits &&
               (r.far_buckets == 1 || (r.far_buckets == 0 && spans >= 16));
 }
 
-void set_tier_args(const bc_graph *g, int wave_deg, int wg_deg, BatchArgs &a)
+void set_tier_args(const bc_graph *g, int wg_deg, BatchArgs &a)
 {
-    a.wave_deg = (uint32_t)wave_deg;
     a.wg_deg = (uint32_t)wg_deg;
     a.hubs = g->maxdeg > wg_deg;
 }
@@ -791,8 +789,8 @@ void launch_batched_pass(bc_graph *g, const ResolvedOptions &r, const int32_t *s
     a.perm = g->perm_dev();
     a.H = r.lds_vertices;
     a.lds_bits = r.lds_bits;
-    set_tier_args(g, r.wave_deg, r.wg_deg, a);
-    a.kahn = r.dep_mode == 1 ? 1 : 0;
+    set_tier_args(g, r.wg_deg, a);
+    a.push = r.dep_mode == 1 ? 1 : 0;
     a.vw = r.vw;
     a.node_parallel = r.node_parallel;
     a.ebc = ebc_dev;
@@ -938,8 +936,6 @@ static void run_plain(bc_graph *g, const ResolvedOptions &r, const int32_t *src_
                 throw bc_error(BC_E_INTERNAL, "plain phase machine did not finish");
         }
         g->plain_gen_hint = g->host_plain->gen;
-        if (g->host_plain->abort)
-            hip_check(launch_plain_clear_infar(a, st), "clear");
     }
     hip_check(hipEventRecord(e1, st), "event");
     read_device_counters(g, st, cnt);

@@ -79,10 +79,10 @@ struct ResolvedOptions {
     int autotune = 0;
     int lds_vertices = 0; // H: distances kept in LDS per source
     int lds_bits = 32;    // width of an LDS distance entry (8, 16 or 32)
-    int dep_mode = 1;     // 1 recorded DAG (Kahn), 2 band pulls
+    int dep_mode = 1;     // 1 push along the recorded DAG, 2 pull over out-arcs
     int vw = 0;           // expansion lanes per vertex (0 adaptive)
     int lane_deg = BC_DEF_LANE_DEG; // lower bound of wave_deg (reported only)
-    int wave_deg = BC_DEF_WAVE_DEG; // count pass: a wave above this many in-arcs
+    int wave_deg = BC_DEF_WAVE_DEG; // plain form's counts: a wave above this many in-arcs
     int wg_deg = BC_HUB_DEG;        // expansion: the whole workgroup above this (batched form)
     int node_parallel = 0;
     int far_buckets = 0;  // batched: 0 auto, 1 far-bucket ring, 2 two-tier pile
@@ -188,7 +188,7 @@ void set_inarc_bound(bc_graph *g, hipStream_t st);
 // used, and its number of buckets.
 void bucket_plan(const bc_graph *g, const ResolvedOptions &r, int &buckets, int &nbk);
 // Degree-tier fields of the batched kernel's arguments.
-void set_tier_args(const bc_graph *g, int wave_deg, int wg_deg, BatchArgs &a);
+void set_tier_args(const bc_graph *g, int wg_deg, BatchArgs &a);
 void read_device_counters(bc_graph *g, hipStream_t st, DevCounters &out);
 // Status of a finished computation from its device counters (throws on an
 // out-of-range source, a tripped iteration bound or a count overflow).

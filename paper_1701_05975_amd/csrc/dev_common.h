@@ -35,25 +35,24 @@ struct VField {
 struct Slab {
     uint32_t *d;       // tentative / final distance, BC_INF = unreached
     VField<int32_t, VREC_STAMP> stamp;
-    VField<int32_t, VREC_INFAR> infar;
-    VField<int32_t, VREC_SCNT> scnt;
+    VField<int32_t, VREC_FLAGS> flags;
+    VField<int32_t, VREC_LEVEL> level;
     VField<int32_t, VREC_PRED1> pred1;
     VField<uint64_t, VREC_SIGMA> sigma;
     VField<double, VREC_DELTA> delta;
     double *bcp;       // per-slab partial centrality (batched form)
-    int32_t *order;    // members of each band, band after band
+    int32_t *order;    // reached vertices, band after band (batched form: level after level)
     int32_t *qa, *qb;  // near queues / pending lists
     int32_t *fa, *fb;  // inner far piles (distance below the pile bound)
     int32_t *oa, *ob;  // outer far piles (distance at or above the pile bound)
-    int32_t *band_off; // band b = order[band_off[b] .. band_off[b+1])
-    int64_t *hdr;      // [0] = last queue tag used by this slab
+    int32_t *band_off; // band (level) b = order[band_off[b] .. band_off[b+1])
+    int64_t *hdr;      // [0] = last queue tag, [1] = last count round of this slab
     uint32_t *ld;      // distances of vertices 0 .. H-1 kept in LDS (batched form)
     int32_t H;         // number of LDS-resident distances (0 = none)
     int32_t w16;       // LDS entries are 16-bit; LDS16_FAR = look in d[]
     int32_t w8;        // LDS entries are 8-bit, relative to base8 (see LDS8_WIN)
     uint32_t base8;    // 8-bit entries: the window's base (a band threshold)
-    int32_t *preds;    // in-row positions of v's DAG in-arcs, at preds[trow[v] ...],
-                       // ended by -1 when fewer than the in-degree
+    int32_t *preds;    // v's DAG predecessors when it has several, at preds[trow[v] ...]
 };
 
 __device__ __forceinline__ Slab slab_at(char *base, const SlabLayout &L, int slot)
@@ -61,7 +60,7 @@ __device__ __forceinline__ Slab slab_at(char *base, const SlabLayout &L, int slo
     char *p = base + (size_t)slot * L.stride;
     Slab s;
     s.d = (uint32_t *)(p + L.d);
-    s.stamp.rec = s.infar.rec = s.scnt.rec = s.pred1.rec = s.sigma.rec = s.delta.rec = p + L.rec;
+    s.stamp.rec = s.flags.rec = s.level.rec = s.pred1.rec = s.sigma.rec = s.delta.rec = p + L.rec;
     s.bcp = (double *)(p + L.bcp);
     s.order = (int32_t *)(p + L.order);
     s.qa = (int32_t *)(p + L.qa);

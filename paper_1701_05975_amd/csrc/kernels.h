@@ -22,14 +22,13 @@ struct BatchArgs {
     int32_t H;                    // distances of internal vertices 0..H-1 kept in LDS
     int32_t lds_bits;             // width of the LDS distance entries: 32, 16 or 8 (8: packed arcs)
     int32_t hubs;                 // the graph has vertices of more than wg_deg arcs
-    int32_t kahn;                 // 1: dependencies along the recorded DAG; 0: band pulls
+    int32_t push;                 // 1: dependencies along the recorded DAG; 0: pulls over out-arcs
     int32_t vw;                   // expansion: 0 adaptive lane/wave, else lanes per vertex
     int32_t node_parallel;        // expansion scans every vertex instead of the queue
     double *ebc;                  // optional edge betweenness output (caller arc order)
     const uint32_t *emap;         // in-row position -> caller arc index
     uint32_t delta;               // band width
-    int lane_max;                 // count/dependency passes: lane up to this many arcs
-    uint32_t wave_deg;            // count pass: more in-arcs than this -> the whole wave
+    int lane_max;                 // count pass: one lane sums up to this many predecessors
     uint32_t wg_deg;              // expansion: more arcs than this -> the whole workgroup
     DevStats *stats;
     unsigned long long *err;      // [0] error bits, [1] first overflowing source index
@@ -64,7 +63,7 @@ struct PlainArgs {
     double *bc_out;
     uint32_t delta;
     int lane_max;
-    uint32_t wave_deg;            // as in BatchArgs
+    uint32_t wave_deg;            // count pass: more in-arcs than this -> the whole wave
     DevStats *stats;
     unsigned long long *err;
 };
@@ -81,7 +80,6 @@ hipError_t launch_plain_source(const PlainArgs &a, bool packed, int grid, int32_
                                long long idx, bool clear_stamps, double *bc_out, hipStream_t st);
 hipError_t launch_plain_steps(const PlainArgs &a, bool packed, int grid, int pairs,
                               hipStream_t st);
-hipError_t launch_plain_clear_infar(const PlainArgs &a, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t *p, size_t count, uint32_t value, hipStream_t st);
 // *out = one past the last vertex v with trow[v + 1] > trow[v] (0 if none)
 hipError_t launch_inarc_bound(const uint32_t *trow, int32_t n, int *out, hipStream_t st);

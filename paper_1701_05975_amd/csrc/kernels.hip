@@ -34,16 +34,19 @@ __device__ __forceinline__ uint32_t sat_add_u32(uint32_t x, uint64_t y)
 }
 
 struct WgCtl {
-    int near_len, next_cnt, order_cnt, far_cnt, kept_cnt, pend_cnt;
+    int near_len, next_cnt, order_cnt, far_cnt, kept_cnt;
+    int fin_cnt[3], pend_cnt[3]; // count rounds, each in turn
     int outer_cnt, okept_cnt, resplit;
     int huge_cnt;
     int32_t huge_q[EXPAND_WG_CAP]; // hubs of the current pass, expanded by the workgroup
     int cur, fcur, ocur;
     int32_t gen, band_gen;
-    uint32_t thr, thr_old, far_min, bound, outer_min;
-    int band_start, nbands;
+    uint32_t thr, thr_old, far_min, bound, bound_old, outer_min;
+    int32_t lvl, lvl_base; // count rounds over the slab's life, and at the source's start
+    int band_start, nbands, nlev;
     int abort;
-    int32_t prev_s; // this slab's previous source whose dependencies are not in bcp yet
+    int32_t prev_s; // this slab's previous source whose dependencies are not added yet
+    double *prev_bc; // and the output they go to (atomic accumulation)
     long long src_idx;
     unsigned long long iters;
     unsigned int bands, srounds, drounds;
@@ -52,7 +55,7 @@ struct WgCtl {
     // next non-empty one (offset from bcur, 0 = none), outer pile must be scanned
     int bcnt[BC_BUCKETS_MAX];
     int32_t bcur;
-    int bnext, forced;
+    int bnext, forced, overflowed; // overflowed: a bucket was full in this source
 };
 
 // Phase timing of one workgroup: thread 0 reads the constant-rate device
@@ -75,8 +78,8 @@ __device__ __forceinline__ void phase_mark(WgCtl &C, long long &t0, int phase)
 // later buckets in the window move into the ring (or stay, if theirs is
 // full), settled entries are dropped.  Then the ring bucket's entries move into
 // the near queue as the band [b delta, (b + 1) delta); entries whose vertex
-// was put in a lower bucket since, or settled in an earlier band, and repeats
-// are skipped.  Returns false once no vertex is left, or when the band bound
+// dropped into a lower bucket since are skipped, and, once a bucket was full,
+// repeats (a vertex then can be in the ring and in the pile).  Returns false once no vertex is left, or when the band bound
 // trips.
 template <int NT>
 __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const BatchArgs &a,
@@ -117,12 +120,14 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
             C.bcur = (int32_t)b;
             C.thr_old = C.thr;
             C.thr = sat_add_u32(0u, (b + 1) * D);
+            C.bound_old = C.bound;
             C.bound = sat_add_u32(0u, (b + (uint64_t)nbk) * D);
             C.gen += 1;
             C.band_gen = C.gen;
             C.near_len = 0;
             C.resplit = C.outer_cnt > 0 &&
                         (C.forced || (uint64_t)(C.outer_min / D) < b + (uint64_t)nbk);
+            C.overflowed |= C.forced;
             if (C.resplit) {
                 C.forced = 0;
                 C.outer_min = BC_INF;
@@ -151,19 +156,18 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
                 v = in[i];
                 dv = dist_get(S, v);
                 const uint32_t b = dv / D;
-                if (b == bcur) {
+                // an entry that dropped below the old bound is in the ring, or
+                // settled, unless a full bucket sent it here
+                const bool here = dv >= C.bound_old || C.overflowed;
+                if (here && b == bcur) {
                     mv = atomic_xchg_i32<WG_SCOPE>(&S.stamp[v], C.gen) != C.gen;
-                } else if (b > bcur) {
+                } else if (here && b > bcur) {
                     keep = true;
                     if ((uint64_t)b < (uint64_t)bcur + nbk) {
                         const int slot = (int)(b % (uint32_t)nbk);
                         const int k = atomicAdd(&C.bcnt[slot], 1);
                         if (k < a.bcap) {
                             S.fa[(size_t)slot * (size_t)a.bcap + (size_t)k] = v;
-                            // the entry is current for bucket b (its key at most b's
-                            // already when the pile took it from a full bucket)
-                            __hip_atomic_fetch_min(&S.pred1[v], BUCKET_KEY(b), __ATOMIC_RELAXED,
-                                                   WG_SCOPE);
                             keep = false;
                         } else {
                             C.forced = 1;
@@ -175,7 +179,7 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
                 // bucket it drops into is full).  Each vertex has at most one
                 // entry in the pile at a time.
                 if (b >= bcur && !keep)
-                    __hip_atomic_fetch_and(&S.infar[v], ~2, __ATOMIC_RELAXED, WG_SCOPE);
+                    __hip_atomic_fetch_and(&S.flags[v], ~VFLAG_OUTER, __ATOMIC_RELAXED, WG_SCOPE);
             }
             if (keep)
                 kmin = dv < kmin ? dv : kmin;
@@ -207,11 +211,13 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
         int32_t v = 0;
         if (i < len) {
             v = in[i];
-            // current exactly when the vertex's least bucket is still this one:
-            // a later push to a lower bucket lowers the key, and the count pass
-            // of the band a vertex settles in overwrites it (no distance read)
-            if (S.pred1[v] == BUCKET_KEY(bcur))
+            // current unless the vertex dropped into a lower bucket since; once
+            // a bucket was full the pile's entries can repeat the ring's
+            mv = dist_get(S, v) >= bcur * D;
+            if (mv && C.overflowed)
                 mv = atomic_xchg_i32<WG_SCOPE>(&S.stamp[v], C.gen) != C.gen;
+            else if (mv && a.node_parallel)
+                S.stamp[v] = C.gen;
         }
         int k = wave_alloc(&C.near_len, mv);
         if (mv)
@@ -227,60 +233,64 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
     return true;
 }
 
-// Runs the count (or dependency) rounds over the members order[b0, b1) of
-// one band inside a workgroup.  Returns false if the round bound tripped.
-template <bool PACKED, int NT, bool SIGMA, bool ATOMIC_BC, bool RECORD>
-__device__ __forceinline__ bool wg_band_rounds(const DevGraph &g, const Slab &S, WgCtl &C, const BatchArgs &a,
-                               int32_t s, long long idx, int b0, int b1, double *bc,
-                               uint64_t &st_arcs, uint64_t &st_dag)
+// Counts the members order[b0, b1) of one band in rounds and leaves them in
+// order[] level by level.  The first round's final vertices go to `fin` (free
+// until the next pile scan) and are copied over the members it read while the
+// second round runs.  Returns false if a round made no progress.
+template <bool PACKED, int NT>
+__device__ __forceinline__ bool wg_count_rounds(const DevGraph &g, const Slab &S, WgCtl &C,
+                                                const BatchArgs &a, long long idx, int b0, int b1,
+                                                int32_t *fin, uint64_t &st_dag)
 {
     const int tid = threadIdx.x;
+    const int32_t base = C.lvl_base, lvl0 = C.lvl;
     const int32_t *items = S.order + b0;
-    int len = b1 - b0;
-    int which = 0;
-    const int cap = len + 2;
+    int len = b1 - b0, done = 0, first = 0;
+    if (tid == 0)
+        C.fin_cnt[0] = C.pend_cnt[0] = 0;
+    __syncthreads();
     for (int round = 0;; ++round) {
+        const int r = round % 3, rn = (round + 1) % 3;
         if (tid == 0)
-            C.pend_cnt = 0;
+            C.fin_cnt[rn] = C.pend_cnt[rn] = 0; // last read before the previous barrier
+        CountCtx cc;
+        cc.items = items;
+        cc.len = len;
+        cc.worker = tid / WAVE;
+        cc.nworkers = NT / WAVE;
+        cc.lane_max = a.lane_max;
+        cc.src_idx = idx;
+        cc.base = base;
+        cc.cur = lvl0 + 1 + round;
+        cc.fin_q = round == 0 ? fin : S.order + b0 + done;
+        cc.fin_cnt = &C.fin_cnt[r];
+        cc.pend_q = round & 1 ? S.qb : S.qa;
+        cc.pend_cnt = &C.pend_cnt[r];
+        cc.err = a.err;
+        cc.item_err = a.item_err;
+        cc.keys = a.ebc == nullptr;
+        cc.positions = a.ebc != nullptr;
+        if (round == 1)
+            for (int i = tid; i < first; i += NT)
+                S.order[b0 + i] = fin[i];
+        count_pass<PACKED, WG_SCOPE>(g, S, cc, st_dag);
         __syncthreads();
-        RoundCtx rc;
-        rc.items = items;
-        rc.len = len;
-        rc.worker = tid / WAVE;
-        rc.nworkers = NT / WAVE;
-        rc.lane_max = a.lane_max;
-        rc.s = s;
-        rc.src_idx = idx;
-        rc.first_round = round == 0;
-        rc.pend_q = which ? S.qb : S.qa;
-        rc.pend_cnt = &C.pend_cnt;
-        rc.err = a.err;
-        rc.item_err = a.item_err;
-        rc.perm = ATOMIC_BC ? a.perm : nullptr;
-        rc.keys = a.ebc == nullptr;
-        rc.band_gen = C.band_gen;
-        rc.wave_deg = a.wave_deg;
-        rc.count_arcs = 0; // counted in the streaming pass of the next initialisation
-        if (SIGMA)
-            sigma_round<PACKED, WG_SCOPE, RECORD>(g, S, rc, st_arcs, st_dag);
-        else
-            delta_round<PACKED, WG_SCOPE, ATOMIC_BC>(g, S, rc, bc);
-        __syncthreads();
-        const int nl = C.pend_cnt;
-        __syncthreads(); // everyone has read pend_cnt before it is touched again
+        const int nf = C.fin_cnt[r], np = C.pend_cnt[r];
+        if (round == 0)
+            first = nf;
+        done += nf;
         if (tid == 0) {
-            if (SIGMA)
-                C.srounds++;
-            else
-                C.drounds++;
+            C.srounds++;
+            C.lvl = lvl0 + 1 + round;
+            C.nlev += 1;
+            S.band_off[C.nlev] = b0 + done;
         }
-        if (nl == 0)
+        if (np == 0)
             return true;
-        if (round + 1 >= cap)
+        if (nf == 0)
             return false;
-        items = which ? S.qb : S.qa;
-        which ^= 1;
-        len = nl;
+        items = cc.pend_q;
+        len = np;
     }
 }
 
@@ -344,6 +354,7 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
     uint64_t st_arcs = 0, st_dag = 0, st_imp = 0;
     if (tid == 0) {
         C.gen = (int32_t)S.hdr[0];
+        C.lvl = (int32_t)S.hdr[1];
         C.prev_s = -1;
         C.iters = 0;
         C.bands = C.srounds = C.drounds = 0;
@@ -370,20 +381,19 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             continue;
         }
         const int32_t s = a.iperm ? a.iperm[s_in] : s_in;
-        // With per-slab partial sums the dependencies are added to bcp while
-        // the next source's initialisation streams over the vertices (below),
-        // instead of one random access per vertex in the dependency pass.
-        double *bc = ATOMIC_BC ? (a.item_out ? a.item_out[idx] : a.bc_out) : nullptr;
-
-        // Queue tags only grow; restart them long before they could wrap.
-        if (C.gen > (1 << 30)) {
-            for (int v = tid; v < n; v += NT)
+        // Queue tags and round numbers only grow; restart them long before
+        // they could wrap.
+        if (C.gen > (1 << 30) || C.lvl > (1 << 30)) {
+            for (int v = tid; v < n; v += NT) {
                 S.stamp[v] = 0;
+                S.level[v] = 0;
+            }
             __syncthreads();
             if (tid == 0)
-                C.gen = 0;
+                C.gen = C.lvl = 0;
         }
-        // Initialisation (Alg. 1): d = inf and sigma = 0 everywhere.
+        // Initialisation (Alg. 1): d = inf everywhere; no vertex is final (its
+        // round number lies below this source's).
         S.base8 = 0;
         if (LB < 32) {
             constexpr int per = 32 / LB;
@@ -397,28 +407,27 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             // d[] of this slab is complete here (the previous source wrote its
             // LDS part back), so the previous source's reached vertices are
             // those with a finite distance: their dependencies go into the
-            // partial sums and their out-degrees into the arc statistic, in
-            // one coalesced pass.  After a completed source the vertices
+            // partial sums (or, with atomic accumulation, the output) and their
+            // out-degrees into the arc statistic, in one coalesced pass.  After a completed source the vertices
             // without in-arcs (from g.n_act on) are untouched but for that
             // source itself, so only [0, n_act) and the source are visited;
             // the launch's first source, and one after an abort, visit all.
             const int32_t ps = C.prev_s;
+            double *const pbc = C.prev_bc;
             auto reset = [&](int v) {
                 if (ps >= 0 && S.d[v] != BC_INF) {
                     st_arcs += g.row[v + 1] - g.row[v];
-                    if (!ATOMIC_BC && v != ps)
-                        S.bcp[v] += S.delta[v];
+                    if (v != ps) {
+                        if (ATOMIC_BC)
+                            unsafeAtomicAdd(&pbc[a.perm ? a.perm[v] : v], S.delta[v]);
+                        else
+                            S.bcp[v] += S.delta[v];
+                    }
                 }
                 if (LB < 32 || v >= S.H)
                     S.d[v] = BC_INF;
-                S.sigma[v] = 0;
-                if (a.kahn)
-                    S.scnt[v] = 0;
-                S.infar[v] = 0; // far-pile flags and tie count start clear
-                if (a.ebc == nullptr)
-                    *key_ptr(S, v) = KEY_NONE; // no predecessor key yet
-                if (BKT)
-                    S.pred1[v] = INT32_MAX; // in no far bucket yet
+                S.flags[v] = 0; // tie count and flags start clear
+                *key_ptr(S, v) = KEY_NONE; // no predecessor key yet
             };
             const int lim = ps >= 0 ? g.n_act : n;
             for (int v = tid; v < lim; v += NT)
@@ -431,12 +440,20 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
         __syncthreads();
         if (tid == 0) {
             dist_set(S, s, 0);
+            // the source is final before the first round, a level of its own
+            C.lvl += 1;
+            C.lvl_base = C.lvl;
+            S.level[s] = C.lvl;
             S.sigma[s] = 1;
+            S.delta[s] = 0.0;
+            S.pred1[s] = -1;
             C.gen += 1;
             S.stamp[s] = C.gen;
             S.qa[0] = s;
             S.order[0] = s;
             S.band_off[0] = 0;
+            S.band_off[1] = 1;
+            C.nlev = 1;
             C.cur = 0;
             C.fcur = 0;
             C.near_len = 1;
@@ -453,8 +470,8 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             C.bound = BKT ? sat_add_u32(0u, (uint64_t)a.nbk * a.delta)
                                 : sat_add_u32(a.delta, (uint64_t)OUTER_BANDS * a.delta);
             C.bcur = 0;
-            C.forced = 0;
-            C.band_start = 0;
+            C.forced = C.overflowed = 0;
+            C.band_start = 1;
             C.nbands = 0;
             C.abort = 0;
             C.iters = 0;
@@ -533,25 +550,16 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 break;
             // The band is closed: its members order[b0, b1) have final distances.
             const int b0 = C.band_start, b1 = C.order_cnt;
-            if (b1 > b0) {
-                const bool ok =
-                    a.kahn ? wg_band_rounds<PACKED, NT, true, ATOMIC_BC, true>(
-                                 g, S, C, a, s, idx, b0, b1, bc, st_arcs, st_dag)
-                           : wg_band_rounds<PACKED, NT, true, ATOMIC_BC, false>(
-                                 g, S, C, a, s, idx, b0, b1, bc, st_arcs, st_dag);
-                if (!ok) {
-                    if (tid == 0)
-                        C.abort = 1;
-                    __syncthreads();
-                    break;
-                }
+            if (b1 > b0 && !wg_count_rounds<PACKED, NT>(g, S, C, a, idx, b0, b1,
+                                                        C.ocur ? S.oa : S.ob, st_dag)) {
+                if (tid == 0)
+                    C.abort = 1;
+                __syncthreads();
+                break;
             }
             phase_mark(C, tmark, 2);
             if (tid == 0) {
-                if (b1 > b0) {
-                    C.nbands += 1;
-                    S.band_off[C.nbands] = b1;
-                }
+                C.nbands += b1 > b0;
                 C.band_start = b1;
             }
             __syncthreads();
@@ -587,6 +595,7 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 C.kept_cnt = 0;
                 C.okept_cnt = 0;
                 C.resplit = C.thr > C.bound && C.outer_cnt > 0;
+                C.bound_old = C.bound;
                 if (C.thr > C.bound) {
                     C.bound = sat_add_u32(C.thr, (uint64_t)OUTER_BANDS * a.delta);
                     if (C.resplit)
@@ -606,7 +615,7 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 op.len = C.outer_cnt;
                 op.worker = tid / WAVE;
                 op.nworkers = NT / WAVE;
-                op.thr_old = C.thr_old;
+                op.bound_old = C.bound_old;
                 op.bound = C.bound;
                 op.inner_q = C.fcur ? S.fb : S.fa;
                 op.inner_cnt = &C.far_cnt;
@@ -633,13 +642,13 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 sp.thr_old = C.thr_old;
                 sp.thr = C.thr;
                 sp.tag = C.gen;
+                sp.set_tags = a.node_parallel;
                 sp.near_q = C.cur ? S.qb : S.qa;
                 sp.near_cnt = &C.near_len;
                 sp.order = S.order;
                 sp.order_cnt = &C.order_cnt;
                 sp.far_out = C.fcur ? S.fa : S.fb;
                 sp.kept_cnt = &C.kept_cnt;
-                sp.clear_flags = 0;
                 uint32_t kmin = BC_INF;
                 split_pass(S, sp, kmin);
                 kmin = wave_min_u32(kmin);
@@ -655,70 +664,33 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             phase_mark(C, tmark, 4);
         }
 
-        // Backward pass (Alg. 3), either band by band in reverse with pulls over
-        // out-arcs, or in Kahn's order over the recorded shortest-path DAG,
-        // from the vertices without successors towards the source.
-        if (!C.abort && !a.kahn) {
-            const int nb = C.nbands;
-            for (int b = nb - 1; b >= 0; --b) {
-                const int b0 = S.band_off[b], b1 = S.band_off[b + 1];
-                if (!wg_band_rounds<PACKED, NT, false, ATOMIC_BC, false>(
-                        g, S, C, a, s, idx, b0, b1, bc, st_arcs, st_dag)) {
-                    if (tid == 0)
-                        C.abort = 1;
-                    break;
+        // Backward pass (Alg. 3): the levels in reverse, down to the source's
+        // own, each adding its terms into its predecessors (or pulling them
+        // over its out-arcs).
+        if (!C.abort) {
+            int hi = C.order_cnt;
+            for (int l = C.nlev - 1; l > 0; --l) {
+                const int lo = S.band_off[l];
+                if (a.push) {
+                    PushCtx pc;
+                    pc.items = S.order + lo;
+                    pc.len = hi - lo;
+                    pc.worker = tid / WAVE;
+                    pc.nworkers = NT / WAVE;
+                    pc.ebc = a.ebc;
+                    pc.emap = a.emap;
+                    push_level<PACKED, WG_SCOPE>(g, S, pc);
+                } else {
+                    pull_level<PACKED>(g, S, S.order + lo, hi - lo, tid / WAVE, NT / WAVE,
+                                       a.lane_max);
                 }
+                hi = lo;
+                __syncthreads();
             }
-        }
-        // Kahn's order band by band, last band first: successor counts cover
-        // only arcs inside a band, and a vertex's successors in later bands
-        // are all done before its own band starts.
-        if (!C.abort && a.kahn) {
-            const int cap = C.order_cnt + 2;
-            int steps = 0;
-            for (int b = C.nbands - 1; b >= 0 && !C.abort; --b) {
-                const int b0 = S.band_off[b], b1 = S.band_off[b + 1];
-                if (tid == 0)
-                    C.pend_cnt = 0;
-                __syncthreads();
-                kahn_leaves(S, S.order + b0, b1 - b0, tid / WAVE, NT / WAVE, S.qa, &C.pend_cnt);
-                __syncthreads();
-                int len = C.pend_cnt;
-                __syncthreads();
-                const int32_t *items = S.qa;
-                int which = 0;
-                while (len > 0) {
-                    if (++steps > cap) {
-                        if (tid == 0)
-                            C.abort = 1;
-                        __syncthreads();
-                        break;
-                    }
-                    if (tid == 0)
-                        C.pend_cnt = 0;
-                    __syncthreads();
-                    KahnCtx kc;
-                    kc.items = items;
-                    kc.len = len;
-                    kc.worker = tid / WAVE;
-                    kc.nworkers = NT / WAVE;
-                    kc.lane_max = a.lane_max;
-                    kc.s = s;
-                    kc.next_q = which ? S.qa : S.qb;
-                    kc.next_cnt = &C.pend_cnt;
-                    kc.perm = ATOMIC_BC ? a.perm : nullptr;
-                    kc.ebc = a.ebc;
-                    kc.emap = a.emap;
-                    kahn_step<PACKED, WG_SCOPE, ATOMIC_BC>(g, S, kc, bc);
-                    __syncthreads();
-                    len = C.pend_cnt;
-                    __syncthreads();
-                    items = which ? S.qa : S.qb;
-                    which ^= 1;
-                    if (tid == 0)
-                        C.drounds++;
-                }
-            }
+            if (!a.push)
+                pull_level<PACKED>(g, S, S.order, 1, tid / WAVE, NT / WAVE, a.lane_max);
+            if (tid == 0)
+                C.drounds += C.nlev - 1;
         }
         phase_mark(C, tmark, 3);
         // The LDS-resident distances go back to the slab so that the slab
@@ -741,9 +713,7 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
         }
         __syncthreads();
         if (C.abort) {
-            // Leave the slab reusable and report; the result is not valid.
-            for (int v = tid; v < n; v += NT)
-                S.infar[v] = 0;
+            // The next initialisation resets the whole slab; the result is not valid.
             if (tid == 0)
                 atomicOr(&a.err[0], (unsigned long long)BC_ERRBIT_INTERNAL);
         }
@@ -752,6 +722,8 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             atomicAdd(&a.stats->bands, (unsigned long long)C.nbands);
             atomicAdd(&a.stats->iterations, C.iters);
             C.prev_s = C.abort ? -1 : s;
+            if (ATOMIC_BC)
+                C.prev_bc = a.item_out ? a.item_out[idx] : a.bc_out;
         }
         __syncthreads();
     }
@@ -759,11 +731,16 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
     // without in-arcs but itself)
     if (C.prev_s >= 0) {
         const int32_t ps = C.prev_s;
+        double *const pbc = C.prev_bc;
         for (int v = tid; v < g.n_act; v += NT)
             if (S.d[v] != BC_INF) {
                 st_arcs += g.row[v + 1] - g.row[v];
-                if (!ATOMIC_BC && v != ps)
-                    S.bcp[v] += S.delta[v];
+                if (v != ps) {
+                    if (ATOMIC_BC)
+                        unsafeAtomicAdd(&pbc[a.perm ? a.perm[v] : v], S.delta[v]);
+                    else
+                        S.bcp[v] += S.delta[v];
+                }
             }
         if (ps >= g.n_act && tid == 0)
             st_arcs += g.row[ps + 1] - g.row[ps];
@@ -790,6 +767,7 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
     }
     if (tid == 0) {
         S.hdr[0] = C.gen;
+        S.hdr[1] = C.lvl;
         atomicAdd(&a.stats->sigma_rounds, (unsigned long long)C.srounds);
         atomicAdd(&a.stats->delta_rounds, (unsigned long long)C.drounds);
         for (int i = 0; i < 5; ++i)
@@ -992,7 +970,7 @@ __global__ __launch_bounds__(256) void k_plain_step(PlainArgs a)
         sp.order_cnt = &c->order_cnt;
         sp.far_out = c->fcur ? S.fa : S.fb;
         sp.kept_cnt = &c->kept_cnt;
-        sp.clear_flags = 1;
+        sp.set_tags = 0;
         uint32_t kmin = BC_INF;
         split_pass(S, sp, kmin);
         kmin = wave_min_u32(kmin);
@@ -1014,13 +992,10 @@ __global__ __launch_bounds__(256) void k_plain_step(PlainArgs a)
         rc.err = a.err;
         rc.item_err = nullptr;
         rc.perm = a.perm;
-        rc.keys = 0; // the plain form records no predecessor keys
-        rc.count_arcs = 1;
-        rc.band_gen = 0;
         rc.wave_deg = a.wave_deg;
         if (phase == PH_SIGMA) {
             uint64_t arcs = 0, dag = 0;
-            sigma_round<PACKED, AG_SCOPE, false>(g, S, rc, arcs, dag);
+            sigma_round<PACKED, AG_SCOPE>(g, S, rc, arcs, dag);
             unsigned long long x = arcs, y = dag;
             for (int o = 32; o > 0; o >>= 1) {
                 x += __shfl_xor(x, o);
@@ -1033,7 +1008,7 @@ __global__ __launch_bounds__(256) void k_plain_step(PlainArgs a)
                     atomicAdd(&a.stats->dag, y);
             }
         } else {
-            delta_round<PACKED, AG_SCOPE, false>(g, S, rc, c->bc_out);
+            delta_round<PACKED, AG_SCOPE>(g, S, rc, c->bc_out);
         }
     }
 }
@@ -1125,13 +1100,6 @@ __global__ void k_plain_control(PlainArgs a)
     }
 }
 
-__global__ void k_plain_clear_infar(PlainArgs a)
-{
-    Slab S = slab_at(a.slab_base, a.L, 0);
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.g.n; v += gridDim.x * blockDim.x)
-        S.infar[v] = 0;
-}
-
 // ---------------------------------------------------------------------------
 // Utilities
 // ---------------------------------------------------------------------------
@@ -1173,10 +1141,11 @@ __global__ void k_slab_reset(char *slab_base, SlabLayout L, int nslabs, int n)
     Slab S = slab_at(slab_base, L, slot);
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
         S.stamp[v] = 0;
-        S.infar[v] = 0;
+        S.flags[v] = 0;
+        S.level[v] = 0;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0)
-        S.hdr[0] = 0;
+        S.hdr[0] = S.hdr[1] = 0;
 }
 
 // Copies one slab's per-source state out, with unreached vertices shown as
@@ -1395,17 +1364,6 @@ hipError_t launch_plain_steps(const PlainArgs &a, bool packed, int grid, int pai
             hipLaunchKernelGGL(k_plain_step<false>, dim3(grid), dim3(256), 0, st, a);
         hipLaunchKernelGGL(k_plain_control, dim3(1), dim3(1), 0, st, a);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_plain_clear_infar(const PlainArgs &a, hipStream_t st)
-{
-    int fb = (a.g.n + 255) / 256;
-    if (fb > 2048)
-        fb = 2048;
-    if (fb < 1)
-        fb = 1;
-    hipLaunchKernelGGL(k_plain_clear_infar, dim3(fb), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 

@@ -6,9 +6,10 @@
 // Mapping of work to lanes (the warp-centric idea of Sec. 3.4 recast for
 // 64-lane wavefronts): the expansion lays the arcs of up to 64 queued vertices
 // out flat over the wave, so that every lane has an arc whatever the degrees
-// are, and a hub's arcs over the whole workgroup; the count pass handles a
-// vertex by one lane, a group of EXPAND_GROUP lanes or the whole wave by its
-// in-degree.  Only queued vertices get lanes (the work-efficient queue of
+// are, and a hub's arcs over the whole workgroup; the batched form's count and
+// dependency passes do the same where a vertex has more than one arc to look
+// at (the plain form's use a lane, a group of lanes or the wave per vertex).
+// Only queued vertices get lanes (the work-efficient queue of
 // Sec. 3.3); a fixed group width and a scan over every vertex (node-parallel)
 // are selectable for comparison.
 #pragma once
@@ -50,9 +51,12 @@ __device__ __forceinline__ uint32_t dist_min(const Slab &S, uint32_t u, uint32_t
                 if (__hip_atomic_compare_exchange_strong(wp, &expect, nw, __ATOMIC_RELAXED,
                                                          __ATOMIC_RELAXED,
                                                          __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                    if (e == LDS8_FAR) // first value that does not fit (h was unreached)
+                    // first value that does not fit (h was unreached), or first that
+                    // does (h was kept in d[]): d[u] orders these two, so that
+                    // exactly one offer sees each earlier value as the old one
+                    if (e == LDS8_FAR || h == LDS8_FAR)
                         return atomic_min_u32<SCOPE>(&S.d[u], v);
-                    return h - 1u < LDS8_WIN ? S.base8 + h - 1u : BC_INF; // d[u] was larger
+                    return h - 1u < LDS8_WIN ? S.base8 + h - 1u : BC_INF;
                 }
                 cur = expect;
             }
@@ -81,9 +85,10 @@ __device__ __forceinline__ uint32_t dist_min(const Slab &S, uint32_t u, uint32_t
             if (__hip_atomic_compare_exchange_strong(wp, &expect, nw, __ATOMIC_RELAXED,
                                                      __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                if (e == LDS16_FAR) // first value that does not fit (h was unreached)
+                // as for the 8-bit entries: d[u] orders the offers around LDS16_FAR
+                if (e == LDS16_FAR || h == LDS16_FAR)
                     return atomic_min_u32<SCOPE>(&S.d[u], v);
-                return h < LDS16_FAR ? h : BC_INF; // d[u] held at least LDS16_FAR
+                return h < LDS16_FAR ? h : BC_INF;
             }
             cur = expect;
         }
@@ -133,11 +138,11 @@ __device__ __forceinline__ void store_f64(double *p, double v)
 //
 // Every arc (v, u, w) of a queued vertex v proposes d[v] + w for u; atomicMin
 // keeps the least.  A lane that lowered d[u] below the band threshold puts u
-// in the next near queue (once per queue, by tag) and, the first time in this
-// band, in the band's member list; a lower value at or above the threshold
-// sends u to the far pile (once, by flag): the inner pile below the pile
-// bound, else the outer pile, which is only scanned when the threshold
-// passes the bound.
+// in the next near queue (once per queue, by tag) and, the first time, in the
+// band's member list; a lower value at or above the threshold sends u to the
+// far pile (once): the inner pile below the pile bound, else the outer pile,
+// which is only scanned when the threshold passes the bound.  What is the
+// first time follows from the value that the minimum replaced.
 // ---------------------------------------------------------------------------
 struct ExpandCtx {
     const int32_t *items;
@@ -165,10 +170,9 @@ struct ExpandCtx {
     uint32_t wg_deg;      // more arcs than this (batched, huge_q set): the whole workgroup
     // Far-bucket ring (batched form, relax<.., true>; else the two-tier pile above).  A far
     // value below `bound` goes to bucket value / bdelta, slot bucket % nbk,
-    // when that bucket is lower than any the vertex was put in before (its
-    // record's pred1 word holds the least so far); a full bucket sends the
-    // vertex to the outer pile and sets *forced, so that the pile is scanned
-    // at the next band change.
+    // when the value it replaces lay in a higher bucket (or beyond the ring);
+    // a full bucket sends the vertex to the outer pile and sets *forced, so
+    // that the pile is scanned at the next band change.
     int32_t *bk;
     int *bcnt;
     uint32_t bdelta;
@@ -179,7 +183,7 @@ struct ExpandCtx {
 // Predecessor keys (batched form).  While distances are being found, the
 // dependency field of a vertex (unused until its count is taken) holds the
 // least (distance << 32 | tail) over the improvements it received, and the
-// bits from TIE_SHIFT up in its far-flags word count the relaxations that
+// bits from TIE_SHIFT up in its flags word count the relaxations that
 // matched its distance at the time (ties).  A relaxation that offers v its
 // final distance comes from a tight arc whose tail is at its own final
 // distance (one from a larger tail distance offers more), and it always
@@ -195,12 +199,11 @@ struct ExpandCtx {
 // which the count pass reads until it writes the vertex's DAG list there.  A
 // vertex whose ties were all kept and whose predecessor tails are all
 // distinct takes its count and its DAG list from the key and those pairs
-// without reading its in-arcs; the list then names tails rather than in-row
-// positions, and VFLAG_TLIST in the far-flags word says so.  A vertex with
+// without reading its in-arcs.  A vertex with
 // more ties, or with a tail seen twice (a second expansion, or parallel tight
 // arcs: the pairs cannot tell these apart), scans its in-arcs.
-#define VFLAG_TLIST 4
-#define VFLAG_SCAN 8 // the count pass found a repeated tail: v scans in every round
+#define VFLAG_OUTER 2 // in the outer far pile (bucket ring only)
+#define VFLAG_LIST 4  // the DAG list (or the only predecessor) of v is recorded
 #define TIE_SHIFT 4
 #define TIE_MAX 7
 #define KEY_NONE (~0ull)
@@ -236,10 +239,11 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
                                              uint64_t &nimp)
 {
     bool imp = false, tie = false;
+    uint32_t was = BC_INF;
     if (cand) {
-        const uint32_t old = dist_min<SCOPE>(S, u, nd);
-        imp = nd < old;
-        tie = nd == old;
+        was = dist_min<SCOPE>(S, u, nd);
+        imp = nd < was;
+        tie = nd == was;
     }
     if (c.keys) {
         if (imp)
@@ -247,9 +251,9 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
                                    __ATOMIC_RELAXED, SCOPE);
         // counting stops past TIE_MAX (beyond it a vertex scans anyway), so
         // the count stays below TIE_MAX + 2 + the threads of the workgroup
-        if (tie && ((uint32_t)__hip_atomic_load(&S.infar[u], __ATOMIC_RELAXED, SCOPE) >>
+        if (tie && ((uint32_t)__hip_atomic_load(&S.flags[u], __ATOMIC_RELAXED, SCOPE) >>
                     TIE_SHIFT) <= TIE_MAX) {
-            const uint32_t t = (uint32_t)__hip_atomic_fetch_add(&S.infar[u], 1 << TIE_SHIFT,
+            const uint32_t t = (uint32_t)__hip_atomic_fetch_add(&S.flags[u], 1 << TIE_SHIFT,
                                                                 __ATOMIC_RELAXED, SCOPE) >>
                                TIE_SHIFT;
             if (t < TIE_MAX) {
@@ -261,27 +265,30 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
             }
         }
     }
+    // The old value says where u stands already: offers to one vertex take
+    // effect one after another, so exactly one of them sees each step down.
     bool pn = false, pm = false, pf = false, po = false;
     int bslot = -1; // far-bucket ring: the slot u goes to
     if (imp) {
         ++nimp;
+        const uint32_t old = was;
         if (nd < c.thr) {
-            int32_t ot = atomic_xchg_i32<SCOPE>(&S.stamp[u], c.tag_next);
-            pn = ot != c.tag_next;
-            pm = ot < c.band_gen;
+            pn = atomic_xchg_i32<SCOPE>(&S.stamp[u], c.tag_next) != c.tag_next;
+            pm = old >= c.thr; // first value below the band threshold
         } else if (nd < c.bound) {
             if (BKT) {
                 const uint32_t b = nd / c.bdelta;
-                if (BUCKET_KEY(b) <
-                    __hip_atomic_fetch_min(&S.pred1[u], BUCKET_KEY(b), __ATOMIC_RELAXED, SCOPE))
+                if (old == BC_INF || old >= (b + 1u) * c.bdelta)
                     bslot = (int)(b % (uint32_t)c.nbk);
             } else {
                 far_min = nd < far_min ? nd : far_min;
-                pf = (atomic_or_i32<SCOPE>(&S.infar[u], 1) & 1) == 0;
+                pf = old >= c.bound;
             }
         } else {
             outer_min = nd < outer_min ? nd : outer_min;
-            po = (atomic_or_i32<SCOPE>(&S.infar[u], 2) & 2) == 0;
+            po = old == BC_INF;
+            if (BKT && po)
+                po = (atomic_or_i32<SCOPE>(&S.flags[u], VFLAG_OUTER) & VFLAG_OUTER) == 0;
         }
     }
     if (BKT && __ballot(bslot >= 0)) {
@@ -292,7 +299,7 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
             } else { // a full bucket: the outer pile keeps u until the next band change
                 *c.forced = 1;
                 outer_min = nd < outer_min ? nd : outer_min;
-                po = (atomic_or_i32<SCOPE>(&S.infar[u], 2) & 2) == 0;
+                po = (atomic_or_i32<SCOPE>(&S.flags[u], VFLAG_OUTER) & VFLAG_OUTER) == 0;
             }
         }
     }
@@ -416,6 +423,25 @@ __device__ __forceinline__ void cand_flush(const Slab &S, const ExpandCtx &c, Ca
     b.cnt = 0;
 }
 
+// The item whose range holds flat position q0 + lane: items 0 .. items-1
+// start at the strictly increasing offsets `off` (each lane its own item's).
+__device__ __forceinline__ int flat_item(uint32_t off, int items, uint32_t q0)
+{
+    const int lane = lane_id();
+    const uint64_t starts =
+        wave_or_u64(lane < items && off >= q0 && off - q0 < WAVE ? 1ull << (off - q0) : 0ull);
+    const int before = __popcll(__ballot(lane < items && off < q0));
+    return before + (int)lanes_below(starts) + (int)((starts >> lane) & 1) - 1;
+}
+
+// The lanes with `have` first, in order (a permutation of the wave); the
+// lane's new place times 4, for ds_permute.
+__device__ __forceinline__ int front_place(uint64_t mask, bool have)
+{
+    const int below = (int)lanes_below(mask);
+    return (have ? below : __popcll(mask) + lane_id() - below) << 2;
+}
+
 // Expansion with the arcs of up to 64 queued vertices laid out flat over the
 // lanes (the degree-aware mapping of Sec. 3.4 carried to single arcs: every
 // lane has an arc whatever the degrees are).  `hubs`: the vertices listed in
@@ -469,8 +495,7 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
         const uint64_t has = __ballot(deg > 0);
         const int items = __popcll(has);
         if (has & (has + 1)) {
-            const int below = (int)lanes_below(has);
-            const int dst = (deg > 0 ? below : items + lane - below) << 2;
+            const int dst = front_place(has, deg > 0);
             v = __builtin_amdgcn_ds_permute(dst, v);
             beg = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)beg);
             dv = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)dv);
@@ -486,12 +511,7 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
 #pragma unroll
             for (int j = 0; j < EXPAND_UNROLL; ++j) {
                 const uint32_t q0 = p0 + WAVE * j, p = q0 + lane;
-                // the item whose arcs hold flat position p: the last one starting at
-                // or before it
-                const uint64_t starts = wave_or_u64(
-                    lane < items && off >= q0 && off - q0 < WAVE ? 1ull << (off - q0) : 0ull);
-                const int before = __popcll(__ballot(lane < items && off < q0));
-                const int it = before + (int)lanes_below(starts) + (int)((starts >> lane) & 1) - 1;
+                const int it = flat_item(off, items, q0);
                 const uint32_t sh = (uint32_t)__shfl((int)shift, it);
                 const uint32_t d = (uint32_t)__shfl((int)dv, it);
                 tl[j] = (uint32_t)__shfl(v, it);
@@ -527,7 +547,8 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
 // Far pile split at a band change.  Entries whose distance dropped below the
 // previous threshold were settled through the near queue already (dropped);
 // entries below the new threshold move to the near queue and become members
-// of the new band; the rest stay in the far pile.
+// of the new band; the rest stay in the far pile.  Each vertex sits at most
+// once in a pile (it enters when its value first drops into the pile's range).
 // ---------------------------------------------------------------------------
 struct SplitCtx {
     const int32_t *far_in;
@@ -535,16 +556,13 @@ struct SplitCtx {
     int worker, nworkers;
     uint32_t thr_old, thr;
     int32_t tag;
+    int set_tags; // give the moved vertices the queue's tag (node-parallel expansion)
     int32_t *near_q;
     int *near_cnt;
     int32_t *order;
     int *order_cnt;
     int32_t *far_out;
     int *kept_cnt;
-    int clear_flags; // clear the pile flag of entries leaving the pile (else the
-                     // caller clears every flag before the next source: a vertex
-                     // that left the pile never returns to it, as its distance
-                     // is now below the threshold and only decreases)
 };
 
 __device__ __forceinline__ void split_pass(const Slab &S, const SplitCtx &c, uint32_t &kept_min)
@@ -562,9 +580,7 @@ __device__ __forceinline__ void split_pass(const Slab &S, const SplitCtx &c, uin
         const bool drop = valid && dv < c.thr_old;
         const bool move = valid && !drop && dv < c.thr;
         const bool keep = valid && !drop && !move;
-        if (c.clear_flags && (drop || move))
-            S.infar[v] &= ~1; // each vertex sits at most once in a pile
-        if (move)
+        if (move && c.set_tags)
             S.stamp[v] = c.tag;
         if (keep)
             kept_min = dv < kept_min ? dv : kept_min;
@@ -581,15 +597,14 @@ __device__ __forceinline__ void split_pass(const Slab &S, const SplitCtx &c, uin
 }
 
 // Outer pile pass, when the band threshold has passed the pile bound: entries
-// already settled are dropped, entries below the new bound join the inner
-// pile (unless already there), the rest stay in the outer pile.  Flags of
-// entries leaving the outer pile are left set (they never return to it; the
-// caller clears every flag before the next source).
+// below the old bound went to the inner pile (or a band) when they dropped
+// below it and are left out, entries below the new bound join the inner pile,
+// the rest stay.
 struct OuterSplitCtx {
     const int32_t *outer_in;
     int len;
     int worker, nworkers;
-    uint32_t thr_old, bound;
+    uint32_t bound_old, bound;
     int32_t *inner_q;
     int *inner_cnt;
     int32_t *outer_out;
@@ -602,21 +617,14 @@ __device__ __forceinline__ void outer_split_pass(const Slab &S, const OuterSplit
     const int lane = lane_id();
     for (int base = c.worker * WAVE; base < c.len; base += c.nworkers * WAVE) {
         const int i = base + lane;
-        const bool valid = i < c.len;
         int32_t v = 0;
         uint32_t dv = 0;
-        int32_t f = 0;
-        if (valid) {
+        if (i < c.len) {
             v = c.outer_in[i];
             dv = dist_get(S, v);
-            f = S.infar[v];
         }
-        const bool drop = valid && dv < c.thr_old;
-        const bool move = valid && !drop && dv < c.bound;
-        const bool keep = valid && !drop && !move;
-        const bool join = move && !(f & 1);
-        if (join)
-            S.infar[v] = f | 1;
+        const bool join = i < c.len && dv >= c.bound_old && dv < c.bound;
+        const bool keep = i < c.len && dv >= c.bound;
         if (keep)
             kept_min = dv < kept_min ? dv : kept_min;
         int k = wave_alloc(c.inner_cnt, join);
@@ -646,159 +654,25 @@ struct RoundCtx {
     int *pend_cnt;
     unsigned long long *err; // [0] error bits, [1] first overflowing source index
     unsigned int *item_err;  // optional per-source-entry overflow flags
-    const int32_t *perm;     // optional: caller's vertex id of each internal vertex, used
-                             // when adding into a caller-indexed output
-    int keys;                // predecessor keys were recorded (count pass shortcut)
-    int32_t band_gen;        // queue tag of the band's first pass: a vertex with a tag at
-                             // least this is a member of the band being counted
+    const int32_t *perm;     // optional: caller's vertex id of each internal vertex
     uint32_t wave_deg;       // more in-arcs than this: the whole wave (else a group of
                              // EXPAND_GROUP lanes above lane_max, one lane below)
-    int count_arcs;          // add each member's out-degree to `arcs` in the first round
-                             // (the batched form counts them in its streaming pass instead)
 };
 
-__device__ __forceinline__ void report_sigma_overflow(const RoundCtx &c)
+__device__ __forceinline__ void report_sigma_overflow(unsigned long long *err, long long src_idx,
+                                                      unsigned int *item_err)
 {
-    atomicOr(&c.err[0], (unsigned long long)BC_ERRBIT_SIGMA);
-    atomicMin((long long *)&c.err[1], c.src_idx);
-    if (c.item_err)
-        c.item_err[c.src_idx] = 1u;
+    atomicOr(&err[0], (unsigned long long)BC_ERRBIT_SIGMA);
+    atomicMin((long long *)&err[1], src_idx);
+    if (item_err)
+        item_err[src_idx] = 1u;
 }
 
 // Path counts (the counting rule of Alg. 2, evaluated by pulling): sigma[v]
 // is the sum of sigma[u] over arcs (u, v, w) with d[u] + w == d[v].  With
 // weights >= 1 every such u has d[u] < d[v], so it belongs to this band or
 // an earlier one.
-//
-// With RECORD, the in-row positions of the tight in-arcs of v are also
-// written to preds[trow[v] ..] (the slice of v's own in-row, so no allocation
-// is needed), ended by -1 when there are fewer than the in-degree; a vertex
-// with a single predecessor keeps it in its record instead.  Successor
-// counts scnt are kept only for DAG arcs inside the band (a predecessor in
-// the same band is stored as -(x + 2)): the dependency pass runs band by band
-// in reverse, so a vertex's successors in later bands are always done before
-// its own band starts.
-// A recorded DAG arc (in-row position at preds[slot]) whose tail lies in the
-// band being counted: count it as a successor of the tail, and mark the entry.
 template <bool PACKED, int SCOPE>
-__device__ __forceinline__ void count_if_same_band(const DevGraph &g, const Slab &S,
-                                                   const RoundCtx &c, uint32_t slot)
-{
-    const int32_t pos = S.preds[slot];
-    uint32_t u, w;
-    arc_at<PACKED>(g.tarc, g.twt, (uint32_t)pos, g.wshift, g.wmask, u, w);
-    if (S.stamp[u] >= c.band_gen) {
-        S.preds[slot] = -(pos + 2);
-        __hip_atomic_fetch_add(&S.scnt[u], 1, __ATOMIC_RELAXED, SCOPE);
-    }
-}
-
-// A DAG list entry for tail t (tails, not in-row positions: VFLAG_TLIST):
-// a tail in the band being counted is stored as -(t + 2) and gains a
-// pending successor.
-template <int SCOPE>
-__device__ __forceinline__ int32_t tail_entry(const Slab &S, const RoundCtx &c, int32_t t)
-{
-    if (S.stamp[t] < c.band_gen)
-        return t;
-    __hip_atomic_fetch_add(&S.scnt[t], 1, __ATOMIC_RELAXED, SCOPE);
-    return -(t + 2);
-}
-
-// The count of v from its key and kept ties (see key_ptr), without reading
-// its in-arcs.  Returns false when v has to scan them (a tie was not kept,
-// or a tail is seen twice);
-// sets pend when a predecessor is not counted yet.  The key's distance is v's
-// final distance: every decrease of d[v] is an improvement and the key keeps
-// the least of them.
-template <int SCOPE, bool RECORD>
-__device__ __forceinline__ bool keyed_count(const DevGraph &g, const Slab &S, const RoundCtx &c,
-                                            int32_t v, bool &pend, uint64_t &dag)
-{
-    const uint64_t key = load_u64<SCOPE>(key_ptr(S, v));
-    const int32_t fl = S.infar[v];
-    const uint32_t nt = (uint32_t)fl >> TIE_SHIFT;
-    if (key == KEY_NONE || nt > TIE_MAX || (fl & VFLAG_SCAN))
-        return false;
-    uint32_t tb = 0, te = 0;
-    if (nt > 0) {
-        tb = g.trow[v];
-        te = g.trow[v + 1];
-        if (tb + 2 * nt > te)
-            return false;
-    }
-    const uint32_t dk = (uint32_t)(key >> 32);
-    const int32_t u0 = (int32_t)(uint32_t)key;
-    // A tail seen twice: scan, in this round and in any later one (a scan
-    // that has to wait for a predecessor has already written over the pairs).
-    bool twice = false;
-    for (uint32_t i = 0; i < nt && !twice; ++i) {
-        if ((uint32_t)S.preds[tb + 2 * i] != dk)
-            continue;
-        const int32_t t = S.preds[tb + 2 * i + 1];
-        twice = t == u0;
-        for (uint32_t j = 0; j < i && !twice; ++j)
-            twice = (uint32_t)S.preds[tb + 2 * j] == dk && S.preds[tb + 2 * j + 1] == t;
-    }
-    if (twice) {
-        S.infar[v] = fl | VFLAG_SCAN;
-        return false;
-    }
-    uint64_t acc = load_u64<SCOPE>(&S.sigma[u0]);
-    bool ready = acc != 0, ovf = false;
-    uint32_t m = 0; // ties at the final distance
-    for (uint32_t i = 0; i < nt && ready; ++i) {
-        if ((uint32_t)S.preds[tb + 2 * i] != dk)
-            continue;
-        const uint64_t su = load_u64<SCOPE>(&S.sigma[S.preds[tb + 2 * i + 1]]);
-        if (su == 0) {
-            ready = false;
-        } else {
-            const uint64_t x = acc + su;
-            ovf |= x < acc;
-            acc = x;
-            ++m;
-        }
-    }
-    if (!ready) {
-        pend = true; // the pairs stay for the next round
-        return true;
-    }
-    if (ovf) {
-        report_sigma_overflow(c);
-        acc = ~0ull;
-    }
-    store_u64<SCOPE>(&S.sigma[v], acc);
-    store_f64<SCOPE>(&S.delta[v], RECORD ? 0.0 : -1.0);
-    dag += 1 + m;
-    if (RECORD) {
-        if (m == 0) { // one predecessor: in the record, no DAG list
-            const int32_t e = tail_entry<SCOPE>(S, c, u0);
-            S.pred1[v] = e;
-        } else {
-            // The list overwrites the pairs from the front: the j-th tail goes
-            // to slot j <= i + 1 after pair i (slots 2i, 2i + 1) has been read,
-            // so no pair is overwritten before it is read.
-            uint32_t j = 1;
-            for (uint32_t i = 0; i < nt; ++i) {
-                const uint32_t di = (uint32_t)S.preds[tb + 2 * i];
-                const int32_t t = S.preds[tb + 2 * i + 1];
-                if (di == dk)
-                    S.preds[tb + j++] = tail_entry<SCOPE>(S, c, t);
-            }
-            S.preds[tb] = tail_entry<SCOPE>(S, c, u0);
-            if (tb + j < te)
-                S.preds[tb + j] = -1;
-            S.pred1[v] = -1;
-            S.infar[v] = fl | VFLAG_TLIST;
-        }
-    } else {
-        S.pred1[v] = -1; // a counted vertex's far-bucket value is gone (see VREC_PRED1)
-    }
-    return true;
-}
-
-template <bool PACKED, int SCOPE, bool RECORD>
 __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, const RoundCtx &c, uint64_t &arcs,
                             uint64_t &dag)
 {
@@ -810,32 +684,21 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
         uint32_t beg = 0, end = 0;
         if (valid) {
             v = c.items[i];
-            if (c.first_round && c.count_arcs)
+            if (c.first_round)
                 arcs += g.row[v + 1] - g.row[v];
         }
         const bool is_src = valid && v == c.s;
         bool pend = false;
-        // A vertex whose predecessors are known from its key and kept ties
-        // takes its count from them (see key_ptr) without reading its
-        // in-arcs; the others scan their in-arcs below.
-        bool keyed = false;
-        if (c.keys && valid && !is_src)
-            keyed = keyed_count<SCOPE, RECORD>(g, S, c, v, pend, dag);
-        if (valid && !keyed) {
+        if (valid) {
             beg = g.trow[v];
             end = g.trow[v + 1];
         }
-        if (is_src) {
-            // sigma[s] = 1 was set at initialisation; s has no DAG predecessors
-            store_f64<SCOPE>(&S.delta[v], RECORD ? 0.0 : -1.0);
-            S.pred1[v] = -1;
-            if (RECORD && end > beg)
-                S.preds[beg] = -1;
-        }
+        if (is_src)
+            store_f64<SCOPE>(&S.delta[v], -1.0); // sigma[s] = 1 was set at initialisation
         const uint32_t deg = end - beg;
-        const bool heavy = valid && !is_src && !keyed && deg > c.wave_deg;
-        const bool mid = valid && !is_src && !keyed && !heavy && deg > (uint32_t)c.lane_max;
-        if (valid && !is_src && !keyed && !heavy && !mid) {
+        const bool heavy = valid && !is_src && deg > c.wave_deg;
+        const bool mid = valid && !is_src && !heavy && deg > (uint32_t)c.lane_max;
+        if (valid && !is_src && !heavy && !mid) {
             const uint32_t dv = dist_get(S, v);
             uint64_t acc = 0;
             bool ready = true, ovf = false;
@@ -862,8 +725,6 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
                             const uint64_t t = acc + su;
                             ovf |= t < acc;
                             acc = t;
-                            if (RECORD) // the in-row position identifies the DAG arc
-                                S.preds[beg + tight] = (int32_t)(e0 + j);
                             ++tight;
                         }
                     }
@@ -871,19 +732,12 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
             }
             if (ready) {
                 if (ovf) {
-                    report_sigma_overflow(c);
+                    report_sigma_overflow(c.err, c.src_idx, c.item_err);
                     acc = ~0ull; // stays non-zero so dependants do not wait forever
                 }
                 store_u64<SCOPE>(&S.sigma[v], acc);
-                store_f64<SCOPE>(&S.delta[v], RECORD ? 0.0 : -1.0);
+                store_f64<SCOPE>(&S.delta[v], -1.0);
                 dag += tight;
-                S.pred1[v] = -1;
-                if (RECORD) {
-                    if (beg + tight < end)
-                        S.preds[beg + tight] = -1;
-                    for (uint32_t j = 0; j < tight; ++j)
-                        count_if_same_band<PACKED, SCOPE>(g, S, c, beg + j);
-                }
             }
             pend = !ready;
         }
@@ -934,8 +788,6 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
                     }
                 }
                 const uint64_t gm = (__ballot(tt) >> gshift) & gbits;
-                if (RECORD && tt)
-                    S.preds[mb + rec + __popcll(gm & ((1ull << sub) - 1))] = (int32_t)e;
                 rec += (uint32_t)__popcll(gm);
                 if ((__ballot(!ready) >> gshift) & gbits)
                     break;
@@ -952,19 +804,13 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
             }
             if (have && gready && sub == 0) {
                 if (ovf) {
-                    report_sigma_overflow(c);
+                    report_sigma_overflow(c.err, c.src_idx, c.item_err);
                     acc = ~0ull;
                 }
                 store_u64<SCOPE>(&S.sigma[mv], acc);
-                store_f64<SCOPE>(&S.delta[mv], RECORD ? 0.0 : -1.0);
+                store_f64<SCOPE>(&S.delta[mv], -1.0);
                 dag += rec;
-                S.pred1[mv] = -1;
-                if (RECORD && mb + rec < me)
-                    S.preds[mb + rec] = -1;
             }
-            if (RECORD && have && gready)
-                for (uint32_t j = sub; j < rec; j += EXPAND_GROUP)
-                    count_if_same_band<PACKED, SCOPE>(g, S, c, mb + j);
             const bool p = have && !gready && sub == 0;
             const int k = wave_alloc(c.pend_cnt, p);
             if (p)
@@ -981,10 +827,8 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
             uint64_t acc = 0;
             bool ready = true, ovf = false;
             uint32_t tight = 0;      // this lane's tight arcs
-            uint32_t recorded = 0;   // tight arcs of the wave so far (uniform)
             for (uint32_t e0 = hb; e0 < he; e0 += WAVE) {
                 const uint32_t e = e0 + lane;
-                bool t = false;
                 if (e < he) {
                     uint32_t u, w;
                     arc_at<PACKED>(g.tarc, g.twt, e, g.wshift, g.wmask, u, w);
@@ -997,15 +841,9 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
                             ovf |= x < acc;
                             acc = x;
                             ++tight;
-                            t = true;
-                            if (RECORD) {
-                                const uint64_t tm = __ballot(true);
-                                S.preds[hb + recorded + lanes_below(tm)] = (int32_t)e;
-                            }
                         }
                     }
                 }
-                recorded += (uint32_t)__popcll(__ballot(t));
                 if (__ballot(!ready))
                     break;
             }
@@ -1014,19 +852,13 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
             tight = wave_sum_u32(tight);
             if (all_ready && lane == 0) {
                 if (ovf) {
-                    report_sigma_overflow(c);
+                    report_sigma_overflow(c.err, c.src_idx, c.item_err);
                     acc = ~0ull;
                 }
                 store_u64<SCOPE>(&S.sigma[hv], acc);
-                store_f64<SCOPE>(&S.delta[hv], RECORD ? 0.0 : -1.0);
+                store_f64<SCOPE>(&S.delta[hv], -1.0);
                 dag += tight;
-                S.pred1[hv] = -1;
-                if (RECORD && hb + tight < he)
-                    S.preds[hb + tight] = -1;
             }
-            if (RECORD && all_ready)
-                for (uint32_t j = lane; j < tight; j += WAVE)
-                    count_if_same_band<PACKED, SCOPE>(g, S, c, hb + j);
             const bool p = !all_ready && lane == 0;
             const int k = wave_alloc(c.pend_cnt, p);
             if (p)
@@ -1038,11 +870,8 @@ __device__ __forceinline__ void sigma_round(const DevGraph &g, const Slab &S, co
 // Dependencies (Sec. 2.1 recursion, Alg. 3): delta[v] is the sum over arcs
 // (v, u, w) with d[u] == d[v] + w of sigma[v] / sigma[u] * (1 + delta[u]);
 // every such u lies in this band or a later one.  A vertex other than the
-// source adds its dependency to the centrality: plainly into `bc` when the
-// caller owns it for this source (ATOMIC_BC false), with an FP64 atomic add
-// otherwise; not at all when `bc` is null (the caller adds the dependencies
-// later, in one streaming pass).
-template <bool PACKED, int SCOPE, bool ATOMIC_BC>
+// source adds its dependency to the centrality (each vertex is one lane's).
+template <bool PACKED, int SCOPE>
 __device__ __forceinline__ void delta_round(const DevGraph &g, const Slab &S, const RoundCtx &c, double *bc)
 {
 #pragma clang fp contract(off)
@@ -1089,12 +918,9 @@ __device__ __forceinline__ void delta_round(const DevGraph &g, const Slab &S, co
             }
             if (ready) {
                 store_f64<SCOPE>(&S.delta[v], acc);
-                if (bc && v != c.s) {
+                if (v != c.s) {
                     const int32_t o = c.perm ? c.perm[v] : v;
-                    if (ATOMIC_BC)
-                        unsafeAtomicAdd(&bc[o], acc);
-                    else
-                        bc[o] += acc;
+                    bc[o] += acc;
                 }
             }
             pend = !ready;
@@ -1132,12 +958,9 @@ __device__ __forceinline__ void delta_round(const DevGraph &g, const Slab &S, co
             acc = wave_sum_f64(acc);
             if (all_ready && lane == 0) {
                 store_f64<SCOPE>(&S.delta[hv], acc);
-                if (bc && hv != c.s) {
+                if (hv != c.s) {
                     const int32_t o = c.perm ? c.perm[hv] : hv;
-                    if (ATOMIC_BC)
-                        unsafeAtomicAdd(&bc[o], acc);
-                    else
-                        bc[o] += acc;
+                    bc[o] += acc;
                 }
             }
             const bool p = !all_ready && lane == 0;
@@ -1149,44 +972,50 @@ __device__ __forceinline__ void delta_round(const DevGraph &g, const Slab &S, co
 }
 
 // ---------------------------------------------------------------------------
-// Dependencies by pushing along the recorded shortest-path DAG (Sec. 2.1
-// recursion, Alg. 3 evaluated in reverse topological order): a vertex whose
-// successors have all added their terms is final; it adds its dependency to
-// the centrality and pushes sigma[u] / sigma[w] * (1 + delta[w]) into every
-// recorded predecessor u, whose successor count drops by one.  A predecessor
-// whose count reaches zero joins the next frontier.
+// Batched form: path counts and dependencies by levels of the shortest-path
+// DAG.
+//
+// A band's members are counted in rounds; a member is final in the first
+// round that finds all its DAG predecessors final in earlier rounds.  Its
+// record then holds that round's number, which only grows over the slab's
+// life, so a predecessor is final exactly when its number lies between the
+// source's first and the current one: one finished in the current round
+// reads as pending whichever of the two its reader sees, and no order
+// between its fields matters.  The vertices of a round form a level: no DAG
+// arc lies inside it.  Levels are appended to order[] one after another, and
+// the dependency pass walks them backwards (Alg. 3): every level adds its
+// terms into its predecessors, and needs neither successor counts nor
+// queues.  Per DAG arc that leaves one atomic; successor counts took two more,
+// and a flag or bucket atomic per improvement went with the piles' entries
+// following from the replaced distance (relax_commit).  Scattered global
+// atomics are what bounds the kernel: 256 workgroups of 1024 threads reach
+// 27 to 31 G/s of them while each stays within 0.8 MB, 18 to 20 G/s beyond,
+// returning or not, 32 or 64 bits, against 50 to 300 G/s for loads; with 7.7
+// per reached vertex a Barabasi-Albert run spent about 160 of its 197 ms at
+// that rate.  Barabasi-Albert n = 100,000, 4096 sources: 169 -> 129 ms; R-MAT
+// scale 20, 1024 sources: 311 -> 261 ms; 1000 x 1000 grid, 256 sources: 108 ->
+// 86 ms (flat expansion with candidate batches -> levels).
+//
+// Predecessors of v, once known (d[v] is final): pred1 >= 0 is the only one;
+// -(m + 1) says that preds[trow[v] ..] lists m of them, as tails, or as
+// in-row positions when edge betweenness is asked for; -1: none (the source).
 // ---------------------------------------------------------------------------
-struct KahnCtx {
+struct CountCtx {
     const int32_t *items;
     int len;
     int worker, nworkers;
-    int lane_max;
-    int32_t s;
-    int32_t *next_q;
-    int *next_cnt;
-    const int32_t *perm; // optional caller-indexed output
-    double *ebc;         // optional edge betweenness (caller arc order)
-    const uint32_t *emap; // in-row position -> caller arc index
+    int lane_max;         // lists up to this long are summed by one lane, longer by the wave
+    long long src_idx;    // index in the source list (error reports)
+    int32_t base, cur;    // round numbers: the source's own level, this round
+    int32_t *fin_q;       // vertices final in this round
+    int *fin_cnt;
+    int32_t *pend_q;      // vertices for the next round
+    int *pend_cnt;
+    unsigned long long *err;
+    unsigned int *item_err;
+    int keys;             // predecessor keys were recorded
+    int positions;        // lists hold in-row positions (edge betweenness)
 };
-
-template <int SCOPE>
-__device__ __forceinline__ bool push_dependency(const Slab &S, int32_t u, double c)
-{
-    __hip_atomic_fetch_add(&S.delta[u], c, __ATOMIC_RELAXED, SCOPE);
-    return __hip_atomic_fetch_sub(&S.scnt[u], 1, __ATOMIC_RELAXED, SCOPE) == 1;
-}
-
-// Adds a dependency term into u.  A predecessor in the same band also has
-// its count of pending successors lowered (true when that reaches zero); one
-// in an earlier band only receives the term, with nothing to wait for.
-template <int SCOPE>
-__device__ __forceinline__ bool push_to(const Slab &S, int32_t u, double c, bool same)
-{
-    if (same)
-        return push_dependency<SCOPE>(S, u, c);
-    __hip_atomic_fetch_add(&S.delta[u], c, __ATOMIC_RELAXED, SCOPE);
-    return false;
-}
 
 // A recorded predecessor: the tail of the in-arc at in-row position pos.
 template <bool PACKED>
@@ -1197,113 +1026,316 @@ __device__ __forceinline__ int32_t pred_vertex(const DevGraph &g, int32_t pos)
     return (int32_t)u;
 }
 
-template <bool PACKED, int SCOPE, bool ATOMIC_BC>
-__device__ __forceinline__ void kahn_step(const DevGraph &g, const Slab &S, const KahnCtx &c, double *bc)
+// Sum of the counts of the m predecessors listed at preds[b] onwards, over
+// the list entries first, first + step, ...; ready turns false when one is
+// not final yet.
+template <bool PACKED>
+__device__ __forceinline__ void list_sum(const DevGraph &g, const Slab &S, const CountCtx &c,
+                                         uint32_t b, uint32_t m, uint32_t first, uint32_t step,
+                                         uint64_t &acc, bool &ready, bool &ovf)
 {
-#pragma clang fp contract(off)
+    for (uint32_t j = first; j < m && ready; j += step) {
+        int32_t u = S.preds[b + j];
+        if (c.positions)
+            u = pred_vertex<PACKED>(g, u);
+        const uint32_t lv = (uint32_t)(S.level[u] - c.base);
+        const uint64_t su = S.sigma[u];
+        if (lv < (uint32_t)(c.cur - c.base)) {
+            const uint64_t x = acc + su;
+            ovf |= x < acc;
+            acc = x;
+        } else {
+            ready = false;
+        }
+    }
+}
+
+template <bool PACKED, int SCOPE>
+__device__ __forceinline__ void count_pass(const DevGraph &g, const Slab &S, const CountCtx &c,
+                                           uint64_t &dag)
+{
     const int lane = lane_id();
-    for (int base = c.worker * WAVE; base < c.len; base += c.nworkers * WAVE) {
+    int chunk = (c.len + c.nworkers - 1) / c.nworkers;
+    chunk = chunk < WAVE ? chunk : WAVE;
+    for (int base = c.worker * chunk; base < c.len; base += c.nworkers * chunk) {
         const int i = base + lane;
-        const bool valid = i < c.len;
-        int32_t w = 0, p1 = -1;
-        uint32_t pb = 0, pe = 0;
-        double dw = 0.0, sw = 1.0;
+        const bool valid = lane < chunk && i < c.len;
+        int32_t v = 0, p1 = -1;
+        uint32_t tb = 0, te = 0;
+        bool scan = false;
         if (valid) {
-            w = c.items[i];
-            p1 = S.pred1[w];
-            dw = load_f64<SCOPE>(&S.delta[w]);
-            if (bc && w != c.s) {
-                const int32_t o = c.perm ? c.perm[w] : w;
-                if (ATOMIC_BC)
-                    unsafeAtomicAdd(&bc[o], dw);
-                else
-                    bc[o] += dw;
+            v = c.items[i];
+            const int32_t fl = S.flags[v];
+            const uint64_t key = *key_ptr(S, v);
+            const uint32_t nt = (uint32_t)fl >> TIE_SHIFT;
+            if (fl & VFLAG_LIST) {
+                p1 = S.pred1[v];
+                if (p1 < 0)
+                    tb = g.trow[v];
+            } else if (c.keys && nt == 0 && key != KEY_NONE) {
+                p1 = (int32_t)(uint32_t)key; // the key's tail alone
+            } else {
+                tb = g.trow[v];
+                te = g.trow[v + 1];
+                scan = true;
+                if (c.keys && nt <= TIE_MAX && key != KEY_NONE && tb + 2 * nt <= te) {
+                    // The pairs at the key's distance name the other tails.  The
+                    // list grows over the pairs from the front: entry j <= i + 1 is
+                    // written after pair i (slots 2i, 2i + 1) was read.
+                    const uint32_t dk = (uint32_t)(key >> 32);
+                    const int32_t u0 = (int32_t)(uint32_t)key;
+                    uint32_t m = 1;
+                    bool twice = false;
+                    for (uint32_t k = 0; k < nt && !twice; ++k) {
+                        const uint32_t dk2 = (uint32_t)S.preds[tb + 2 * k];
+                        const int32_t t = S.preds[tb + 2 * k + 1];
+                        if (dk2 != dk)
+                            continue;
+                        twice = t == u0;
+                        for (uint32_t j = 1; j < m; ++j)
+                            twice |= S.preds[tb + j] == t;
+                        S.preds[tb + m] = t;
+                        ++m;
+                    }
+                    if (!twice) { // else a tail is seen twice: scan
+                        scan = false;
+                        if (m == 1) {
+                            p1 = u0;
+                        } else {
+                            S.preds[tb] = u0;
+                            p1 = -(int32_t)(m + 1);
+                        }
+                        S.pred1[v] = p1;
+                        S.flags[v] = fl | VFLAG_LIST;
+                    }
+                }
             }
         }
-        // A lane walks up to lane_max recorded predecessors; the rest of a
-        // longer list is finished by the whole wave.
-        bool more = false;
-        if (valid && p1 != -1) { // the only predecessor, kept in the record
-            // sigma[w] was copied from sigma[u], so their ratio is exactly 1
-            const double term = 1.0 + dw;
-            const int32_t u = p1 < 0 ? -(p1 + 2) : p1;
-            const bool fin = push_to<SCOPE>(S, u, term, p1 < 0);
-            const int k = wave_alloc(c.next_cnt, fin);
-            if (fin)
-                c.next_q[k] = u;
-        } else if (valid) { // the list in preds[], at w's in-row
-            pb = g.trow[w];
-            pe = g.trow[w + 1];
-            sw = (double)S.sigma[w];
-            // a list of tails (at most TIE_MAX + 1) is walked by the lane whole
-            const bool tails = (S.infar[w] & VFLAG_TLIST) != 0;
-            const uint32_t lim = !tails && pe - pb > (uint32_t)c.lane_max ? pb + c.lane_max : pe;
-            uint32_t j = pb;
-            for (; j < lim; ++j) {
-                const int32_t raw = S.preds[j];
-                if (raw == -1)
-                    break;
-                const int32_t pos = raw < 0 ? -(raw + 2) : raw;
-                const int32_t u = tails ? pos : pred_vertex<PACKED>(g, pos);
-                const double term = (double)S.sigma[u] / sw * (1.0 + dw);
-                if (c.ebc) // the term is the source's dependency on the arc u -> w
-                    unsafeAtomicAdd(&c.ebc[c.emap[pos]], term);
-                const bool fin = push_to<SCOPE>(S, u, term, raw < 0);
-                const int k = wave_alloc(c.next_cnt, fin);
-                if (fin)
-                    c.next_q[k] = u;
+        // The others test their in-arcs, laid out flat over the lanes, and list
+        // the tight ones.
+        const uint64_t sm = __ballot(scan);
+        if (sm) {
+            const int items = __popcll(sm);
+            const int dst = front_place(sm, scan);
+            const int32_t sv = __builtin_amdgcn_ds_permute(dst, v);
+            const uint32_t sb = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)tb);
+            const uint32_t se = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)te);
+            const bool mine = lane < items;
+            const uint32_t sd = mine ? dist_get(S, sv) : 0u;
+            const uint32_t deg = mine ? se - sb : 0u;
+            const uint32_t incl = wave_incl_sum_u32(deg);
+            const uint32_t off = incl - deg;
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+            uint32_t m = 0; // tight arcs of the lane's item so far
+            for (uint32_t q0 = 0; q0 < total; q0 += WAVE) {
+                const int it = flat_item(off, items, q0);
+                const uint32_t p = q0 + lane;
+                const uint32_t ib = (uint32_t)__shfl((int)sb, it);
+                const uint32_t io = (uint32_t)__shfl((int)off, it);
+                const uint32_t id = (uint32_t)__shfl((int)sd, it);
+                const uint32_t im = (uint32_t)__shfl((int)m, it);
+                bool tight = false;
+                uint32_t u = 0, w = 0;
+                if (p < total) {
+                    arc_at<PACKED>(g.tarc, g.twt, ib + (p - io), g.wshift, g.wmask, u, w);
+                    tight = dist_get(S, u) + w == id;
+                }
+                const uint64_t tm = __ballot(tight);
+                // the item's lanes start at flat position io (or earlier than q0)
+                const uint32_t lo = io > q0 ? io - q0 : 0u;
+                if (tight)
+                    S.preds[ib + im + __popcll(tm & ((1ull << lane) - (1ull << lo)))] =
+                        c.positions ? (int32_t)(ib + (p - io)) : (int32_t)u;
+                if (mine && off < q0 + WAVE && off + deg > q0) {
+                    const uint32_t a = off > q0 ? off - q0 : 0u;
+                    const uint32_t z = off + deg - q0;
+                    const uint64_t upto = z >= WAVE ? ~0ull : (1ull << z) - 1;
+                    m += (uint32_t)__popcll(tm & upto & ~((1ull << a) - 1));
+                }
             }
-            more = j == lim && lim < pe;
-            pb = lim;
+            // the lists were written by other lanes of this wave
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const uint32_t mm = (uint32_t)__shfl((int)m, dst >> 2);
+            if (scan) {
+                p1 = mm == 1 && !c.positions ? S.preds[tb] : -(int32_t)(mm + 1);
+                S.pred1[v] = p1;
+                S.flags[v] = VFLAG_LIST | (S.flags[v] & VFLAG_OUTER);
+            }
         }
-        uint64_t hm = __ballot(more);
+        uint64_t acc = 0;
+        bool ready = false, ovf = false;
+        uint32_t m = 0;
+        bool wide = false;
+        if (valid && p1 >= 0) {
+            const uint32_t lv = (uint32_t)(S.level[p1] - c.base);
+            acc = S.sigma[p1];
+            ready = lv < (uint32_t)(c.cur - c.base);
+            m = 1;
+        } else if (valid) {
+            m = (uint32_t)(-p1 - 1);
+            wide = m > (uint32_t)c.lane_max;
+            ready = m > 0;
+            if (!wide)
+                list_sum<PACKED>(g, S, c, tb, m, 0, 1, acc, ready, ovf);
+        }
+        uint64_t hm = __ballot(wide);
         while (hm) {
             const int l = __ffsll((unsigned long long)hm) - 1;
             hm &= hm - 1;
-            const uint32_t hb = (uint32_t)__shfl((int)pb, l);
-            const uint32_t he = (uint32_t)__shfl((int)pe, l);
-            const double hd = __shfl(dw, l);
-            const double hs = __shfl(sw, l);
-            for (uint32_t e0 = hb; e0 < he; e0 += WAVE) {
-                const uint32_t e = e0 + lane;
-                const int32_t raw = e < he ? S.preds[e] : -1;
-                const uint64_t endm = __ballot(raw == -1);
-                const int stop = endm ? __ffsll((unsigned long long)endm) - 1 : WAVE;
-                bool fin = false;
-                int32_t u = 0;
-                if (lane < stop) {
-                    const int32_t pos = raw < 0 ? -(raw + 2) : raw;
-                    u = pred_vertex<PACKED>(g, pos);
+            const uint32_t hb = (uint32_t)__shfl((int)tb, l);
+            const uint32_t hn = (uint32_t)__shfl((int)m, l);
+            uint64_t x = 0;
+            bool r = true, o = false;
+            list_sum<PACKED>(g, S, c, hb, hn, (uint32_t)lane, WAVE, x, r, o);
+            const bool all = __ballot(!r) == 0;
+            x = wave_sum_u64_checked(x, o);
+            if (lane == l) {
+                acc = x;
+                ready = all;
+                ovf = o;
+            }
+        }
+        if (valid && ready) {
+            if (ovf) {
+                report_sigma_overflow(c.err, c.src_idx, c.item_err);
+                acc = ~0ull;
+            }
+            S.level[v] = c.cur;
+            S.pred1[v] = p1;
+            S.sigma[v] = acc;
+            S.delta[v] = 0.0;
+            dag += m;
+        }
+        int k = wave_alloc(c.fin_cnt, valid && ready);
+        if (valid && ready)
+            c.fin_q[k] = v;
+        k = wave_alloc(c.pend_cnt, valid && !ready);
+        if (valid && !ready)
+            c.pend_q[k] = v;
+    }
+}
+
+// One level's dependencies (Sec. 2.1 recursion, Alg. 3): every member w is
+// final and adds sigma[u] / sigma[w] * (1 + delta[w]) into each recorded
+// predecessor u.
+struct PushCtx {
+    const int32_t *items;
+    int len;
+    int worker, nworkers;
+    double *ebc;          // optional edge betweenness (caller arc order; lists hold positions)
+    const uint32_t *emap; // in-row position -> caller arc index
+};
+
+template <bool PACKED, int SCOPE>
+__device__ __forceinline__ void push_level(const DevGraph &g, const Slab &S, const PushCtx &c)
+{
+#pragma clang fp contract(off)
+    const int lane = lane_id();
+    int chunk = (c.len + c.nworkers - 1) / c.nworkers;
+    chunk = chunk < WAVE ? chunk : WAVE;
+    for (int base = c.worker * chunk; base < c.len; base += c.nworkers * chunk) {
+        const int i = base + lane;
+        const bool valid = lane < chunk && i < c.len;
+        int32_t w = 0, p1 = -1;
+        double dw = 0.0;
+        if (valid) {
+            w = c.items[i];
+            p1 = S.pred1[w];
+            dw = S.delta[w];
+        }
+        // the only predecessor's count was copied: the ratio is exactly 1
+        if (valid && p1 >= 0)
+            __hip_atomic_fetch_add(&S.delta[p1], 1.0 + dw, __ATOMIC_RELAXED, SCOPE);
+        const bool list = valid && p1 < -1;
+        const uint64_t lm = __ballot(list);
+        if (lm) {
+            uint32_t tb = 0;
+            double sw = 1.0;
+            if (list) {
+                tb = g.trow[w];
+                sw = (double)S.sigma[w];
+            }
+            const int items = __popcll(lm);
+            const int dst = front_place(lm, list);
+            const uint32_t sb = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)tb);
+            const int from = __builtin_amdgcn_ds_permute(dst, lane);
+            const int fp = __shfl(p1, from);
+            const uint32_t deg = lane < items ? (uint32_t)(-fp - 1) : 0u;
+            const uint32_t incl = wave_incl_sum_u32(deg);
+            const uint32_t off = incl - deg;
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+            const uint32_t shift = sb - off;
+            for (uint32_t q0 = 0; q0 < total; q0 += WAVE) {
+                const int it = flat_item(off, items, q0);
+                const uint32_t p = q0 + lane;
+                const uint32_t sh = (uint32_t)__shfl((int)shift, it);
+                const int src = __shfl(from, it);
+                const double hd = __shfl(dw, src);
+                const double hs = __shfl(sw, src);
+                if (p < total) {
+                    const int32_t e = S.preds[p + sh];
+                    const int32_t u = c.ebc ? pred_vertex<PACKED>(g, e) : e;
                     const double term = (double)S.sigma[u] / hs * (1.0 + hd);
-                    if (c.ebc)
-                        unsafeAtomicAdd(&c.ebc[c.emap[pos]], term);
-                    fin = push_to<SCOPE>(S, u, term, raw < 0);
+                    if (c.ebc) // the term is the source's dependency on the arc u -> w
+                        unsafeAtomicAdd(&c.ebc[c.emap[e]], term);
+                    __hip_atomic_fetch_add(&S.delta[u], term, __ATOMIC_RELAXED, SCOPE);
                 }
-                const int k = wave_alloc(c.next_cnt, fin);
-                if (fin)
-                    c.next_q[k] = u;
-                if (endm)
-                    break;
             }
         }
     }
 }
 
-// Members with no DAG successor left in their band start the band's dependency pass.
-__device__ __forceinline__ void kahn_leaves(const Slab &S, const int32_t *order, int n_r, int worker,
-                                            int nworkers, int32_t *q, int *cnt)
+// One level's dependencies by pulling over the out-arcs: every successor lies
+// in a later level, whose dependencies are final.
+template <bool PACKED>
+__device__ __forceinline__ void pull_level(const DevGraph &g, const Slab &S, const int32_t *items,
+                                           int len, int worker, int nworkers, int lane_max)
 {
+#pragma clang fp contract(off)
     const int lane = lane_id();
-    for (int base = worker * WAVE; base < n_r; base += nworkers * WAVE) {
+    for (int base = worker * WAVE; base < len; base += nworkers * WAVE) {
         const int i = base + lane;
+        const bool valid = i < len;
         int32_t v = 0;
-        bool leaf = false;
-        if (i < n_r) {
-            v = order[i];
-            leaf = S.scnt[v] == 0;
+        uint32_t beg = 0, end = 0;
+        if (valid) {
+            v = items[i];
+            beg = g.row[v];
+            end = g.row[v + 1];
         }
-        const int k = wave_alloc(cnt, leaf);
-        if (leaf)
-            q[k] = v;
+        const bool heavy = valid && end - beg > (uint32_t)lane_max;
+        auto term = [&](uint32_t e, uint32_t dv, double sv) {
+            uint32_t u, w;
+            arc_at<PACKED>(g.arc, g.wt, e, g.wshift, g.wmask, u, w);
+            const uint32_t du = dist_get(S, u);
+            return du != BC_INF && du == dv + w ? sv / (double)S.sigma[u] * (1.0 + S.delta[u])
+                                                : 0.0;
+        };
+        if (valid && !heavy) {
+            const uint32_t dv = dist_get(S, v);
+            const double sv = (double)S.sigma[v];
+            double acc = 0.0;
+            for (uint32_t e = beg; e < end; ++e)
+                acc += term(e, dv, sv);
+            S.delta[v] = acc;
+        }
+        uint64_t hm = __ballot(heavy);
+        while (hm) {
+            const int l = __ffsll((unsigned long long)hm) - 1;
+            hm &= hm - 1;
+            const int32_t hv = __shfl(v, l);
+            const uint32_t hb = (uint32_t)__shfl((int)beg, l);
+            const uint32_t he = (uint32_t)__shfl((int)end, l);
+            const uint32_t dv = dist_get(S, hv);
+            const double sv = (double)S.sigma[hv];
+            double acc = 0.0;
+            for (uint32_t e = hb + lane; e < he; e += WAVE)
+                acc += term(e, dv, sv);
+            acc = wave_sum_f64(acc);
+            if (lane == 0)
+                S.delta[hv] = acc;
+        }
     }
 }

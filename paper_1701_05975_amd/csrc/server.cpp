@@ -195,8 +195,8 @@ class HipExec {
         a.perm = g->perm_dev();
         a.H = c->lds_vertices;
         a.lds_bits = c->lds_bits;
-        set_tier_args(g, tier_for(g, 1), tier_for(g, 2), a);
-        a.kahn = dep_mode_for(g) == 1 ? 1 : 0;
+        set_tier_args(g, tier_for(g, 2), a);
+        a.push = dep_mode_for(g) == 1 ? 1 : 0;
         a.ebc = nullptr;
         a.emap = nullptr;
         a.vw = opts_.compute.virtual_warp;
@@ -320,7 +320,7 @@ class HipExec {
             return opts_.compute.lane_max_deg;
         return g->tuned.valid ? g->tuned.lane_max : 32;
     }
-    // degree tiers: 1 a wave per counted vertex, 2 the workgroup per hub
+    // degree tiers: 2 is the workgroup per hub
     int tier_for(bc_graph *g, int which) const
     {
         const bc_options &o = opts_.compute;

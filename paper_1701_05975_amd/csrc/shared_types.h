@@ -50,18 +50,13 @@ struct DevGraph {
 // one line instead of one line per field.  Record layout:
 // ---------------------------------------------------------------------------
 #define VREC_BYTES 32
-#define VREC_STAMP 0  // i32 tag of the latest near queue the vertex entered
-#define VREC_INFAR 4  // i32 bit 0: in the inner far pile; bit 1: in the outer far pile
-#define VREC_SCNT 8   // i32 shortest-path-DAG successors not yet accumulated
-#define VREC_PRED1 12 // i32 the only DAG predecessor, or -1: the list in preds[]; before the
-                      // vertex is counted (bucket ring), BUCKET_KEY of the least far bucket
-                      // it was put in: below every value the count pass writes, so a ring
-                      // entry is current exactly when its bucket's key is there
-// Ring bucket b as kept in the record: below every predecessor encoding while
-// buckets and vertex ids stay below 2^30 (the ring is only planned then).
-#define BUCKET_KEY(b) ((int32_t)((uint32_t)INT32_MIN + (uint32_t)(b)))
-#define VREC_SIGMA 16 // u64 shortest-path count (0 = not yet final in the count pass)
-#define VREC_DELTA 24 // f64 dependency (negative = not yet final in the pull pass)
+#define VREC_STAMP 0  // i32 tag of the latest near queue an improvement put the vertex in
+#define VREC_FLAGS 4  // i32 flags, and the count of ties (VFLAG_*, TIE_SHIFT)
+#define VREC_LEVEL 8  // i32 number of the count round the vertex became final in
+#define VREC_PRED1 12 // i32 the only DAG predecessor, or -(m + 1): m of them in preds[]
+#define VREC_SIGMA 16 // u64 shortest-path count (plain form: 0 = not yet final)
+#define VREC_DELTA 24 // f64 dependency (plain form: negative = not yet final); before the
+                      // vertex is counted its predecessor key (batched form)
 
 // Byte offsets of the slab arrays inside one slot (all 256-byte aligned).
 struct SlabLayout {
