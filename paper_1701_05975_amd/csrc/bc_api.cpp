@@ -580,8 +580,9 @@ void batched_lds_plan(const bc_graph *g, int nt, bool atomic_bc, int requested, 
     if (want_slabs > 0)
         occ = (int)std::min<int64_t>(occ, (want_slabs + g->num_cus - 1) / g->num_cus);
     const size_t lds_cu = 160 * 1024, reserve = 2 * 1024;
-    int cap = (int)((lds_cu / (size_t)std::max(occ, 1) - reserve) / (size_t)(bits / 8));
-    cap &= ~3;
+    // an entry and a queue bit per vertex
+    int cap = (int)((lds_cu / (size_t)std::max(occ, 1) - reserve) * 8 / (size_t)(bits + 1));
+    cap &= ~31;
     if (requested < 0)
         H = 0;
     else if (requested > 0)

@@ -72,7 +72,8 @@ hipError_t launch_batched(const BatchArgs &a, bool packed, int nt, bool atomic_b
                           hipStream_t st);
 int batched_blocks_per_cu_lds(bool packed, int nt, bool atomic_bc, int lds_bits, size_t lds_bytes);
 int batched_blocks_per_cu(bool packed, int nt, bool atomic_bc, int lds_bits);
-// dynamic LDS of a batched launch: H resident distances of lds_bits each
+// dynamic LDS of a batched launch: H resident distances of lds_bits each, and a
+// queue bit each
 size_t batched_lds_bytes(int H, int lds_bits);
 hipError_t launch_reduce_partials(char *slab_base, const SlabLayout &L, int nslabs, int n,
                                   double *out, const int32_t *perm, hipStream_t st);

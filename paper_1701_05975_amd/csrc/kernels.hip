@@ -160,7 +160,8 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
                 // settled, unless a full bucket sent it here
                 const bool here = dv >= C.bound_old || C.overflowed;
                 if (here && b == bcur) {
-                    mv = atomic_xchg_i32<WG_SCOPE>(&S.stamp[v], C.gen) != C.gen;
+                    mv = v < S.HQ ? qbit_set(S, (uint32_t)v)
+                                  : atomic_xchg_i32<WG_SCOPE>(&S.stamp[v], C.gen) != C.gen;
                 } else if (here && b > bcur) {
                     keep = true;
                     if ((uint64_t)b < (uint64_t)bcur + nbk) {
@@ -214,7 +215,9 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
             // current unless the vertex dropped into a lower bucket since; once
             // a bucket was full the pile's entries can repeat the ring's
             mv = dist_get(S, v) >= bcur * D;
-            if (mv && C.overflowed)
+            if (mv && v < S.HQ)
+                mv = qbit_set(S, (uint32_t)v);
+            else if (mv && C.overflowed)
                 mv = atomic_xchg_i32<WG_SCOPE>(&S.stamp[v], C.gen) != C.gen;
             else if (mv && a.node_parallel)
                 S.stamp[v] = C.gen;
@@ -345,6 +348,8 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
     Slab S = slab_at(a.slab_base, a.L, blockIdx.x);
     S.ld = lds_dist;
     S.H = a.H;
+    S.qbit = lds_dist + (a.H + 32 / LB - 1) / (32 / LB);
+    S.HQ = a.node_parallel ? 0 : a.H; // node-parallel expansion finds its vertices by tag
     // compile-time constants: each instantiation keeps one distance path
     S.w16 = LB == 16;
     S.w8 = LB == 8;
@@ -395,6 +400,8 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
         // Initialisation (Alg. 1): d = inf everywhere; no vertex is final (its
         // round number lies below this source's).
         S.base8 = 0;
+        for (int v = tid; v < (S.HQ + 31) / 32; v += NT)
+            S.qbit[v] = 0;
         if (LB < 32) {
             constexpr int per = 32 / LB;
             for (int v = tid; v < (S.H + per - 1) / per; v += NT)
@@ -1227,7 +1234,7 @@ __global__ void k_dynamic_apply(double *bc, const double *before, const double *
 size_t batched_lds_bytes(int H, int lb)
 {
     const int per = 32 / lb;
-    return (size_t)((H + per - 1) / per) * 4;
+    return (size_t)((H + per - 1) / per + (H + 31) / 32) * 4; // entries, then one bit each
 }
 
 template <bool PACKED, int NT, bool ATOMIC, int LB, bool BKT>

@@ -246,9 +246,17 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
         tie = nd == was;
     }
     if (c.keys) {
-        if (imp)
-            __hip_atomic_fetch_min(key_ptr(S, (int32_t)u), (uint64_t)nd << 32 | tail,
-                                   __ATOMIC_RELAXED, SCOPE);
+        if (imp) {
+            // A resident vertex's improvements follow one another in LDS, so its
+            // last store is nearly always that of the least distance: the count
+            // pass compares the two and scans the in-arcs if it is not.  The
+            // others' check would cost a random read, as much as the atomic.
+            const uint64_t key = (uint64_t)nd << 32 | tail;
+            if ((int32_t)u < S.H)
+                __hip_atomic_store(key_ptr(S, (int32_t)u), key, __ATOMIC_RELAXED, SCOPE);
+            else
+                __hip_atomic_fetch_min(key_ptr(S, (int32_t)u), key, __ATOMIC_RELAXED, SCOPE);
+        }
         // counting stops past TIE_MAX (beyond it a vertex scans anyway), so
         // the count stays below TIE_MAX + 2 + the threads of the workgroup
         if (tie && ((uint32_t)__hip_atomic_load(&S.flags[u], __ATOMIC_RELAXED, SCOPE) >>
@@ -273,7 +281,9 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
         ++nimp;
         const uint32_t old = was;
         if (nd < c.thr) {
-            pn = atomic_xchg_i32<SCOPE>(&S.stamp[u], c.tag_next) != c.tag_next;
+            pn = (int32_t)u < S.HQ
+                     ? qbit_set(S, u)
+                     : atomic_xchg_i32<SCOPE>(&S.stamp[u], c.tag_next) != c.tag_next;
             pm = old >= c.thr; // first value below the band threshold
         } else if (nd < c.bound) {
             if (BKT) {
@@ -350,6 +360,8 @@ __device__ __forceinline__ void expand_pass_vw(const DevGraph &g, const Slab &S,
         if (valid) {
             beg = g.row[v];
             end = g.row[v + 1];
+            if (v < S.HQ && sub == 0)
+                qbit_clear(S, (uint32_t)v);
             dv = dist_get(S, v);
         }
         for (uint32_t e = beg + sub; e < end; e += W) {
@@ -479,6 +491,8 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
             if (valid) {
                 beg = g.row[v];
                 end = g.row[v + 1];
+                if (v < S.HQ)
+                    qbit_clear(S, (uint32_t)v);
                 dv = dist_get(S, v);
             }
         }
@@ -580,7 +594,9 @@ __device__ __forceinline__ void split_pass(const Slab &S, const SplitCtx &c, uin
         const bool drop = valid && dv < c.thr_old;
         const bool move = valid && !drop && dv < c.thr;
         const bool keep = valid && !drop && !move;
-        if (move && c.set_tags)
+        if (move && v < S.HQ)
+            qbit_set(S, (uint32_t)v);
+        else if (move && c.set_tags)
             S.stamp[v] = c.tag;
         if (keep)
             kept_min = dv < kept_min ? dv : kept_min;
@@ -1068,17 +1084,21 @@ __device__ __forceinline__ void count_pass(const DevGraph &g, const Slab &S, con
             const int32_t fl = S.flags[v];
             const uint64_t key = *key_ptr(S, v);
             const uint32_t nt = (uint32_t)fl >> TIE_SHIFT;
+            // a resident vertex's key is the last one stored: of the final
+            // distance, but for a race between two improvements
+            const bool keyed = c.keys && key != KEY_NONE &&
+                               (v >= S.H || (uint32_t)(key >> 32) == dist_get(S, (uint32_t)v));
             if (fl & VFLAG_LIST) {
                 p1 = S.pred1[v];
                 if (p1 < 0)
                     tb = g.trow[v];
-            } else if (c.keys && nt == 0 && key != KEY_NONE) {
+            } else if (keyed && nt == 0) {
                 p1 = (int32_t)(uint32_t)key; // the key's tail alone
             } else {
                 tb = g.trow[v];
                 te = g.trow[v + 1];
                 scan = true;
-                if (c.keys && nt <= TIE_MAX && key != KEY_NONE && tb + 2 * nt <= te) {
+                if (keyed && nt <= TIE_MAX && tb + 2 * nt <= te) {
                     // The pairs at the key's distance name the other tails.  The
                     // list grows over the pairs from the front: entry j <= i + 1 is
                     // written after pair i (slots 2i, 2i + 1) was read.
