@@ -579,7 +579,7 @@ void batched_lds_plan(const bc_graph *g, int nt, bool atomic_bc, int requested, 
     int occ = batched_blocks_per_cu(g->packed, nt, atomic_bc, bits);
     if (want_slabs > 0)
         occ = (int)std::min<int64_t>(occ, (want_slabs + g->num_cus - 1) / g->num_cus);
-    const size_t lds_cu = 160 * 1024, reserve = 2 * 1024;
+    const size_t lds_cu = 160 * 1024, reserve = BATCHED_LDS_CTL;
     // an entry and a queue bit per vertex
     int cap = (int)((lds_cu / (size_t)std::max(occ, 1) - reserve) * 8 / (size_t)(bits + 1));
     cap &= ~31;

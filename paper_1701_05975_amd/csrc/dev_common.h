@@ -159,6 +159,54 @@ __device__ __forceinline__ uint32_t dist_peek(const Slab &S, uint32_t u)
     return dist_get(S, u);
 }
 
+// dist_peek of N vertices, without a branch around any load, so that the loads
+// of all N are in flight together: a lane that needs no d[] entry reads the
+// first one, and a wave whose lanes all hold theirs in LDS reads none.
+template <int N>
+__device__ __forceinline__ void dist_peek_n(const Slab &S, const uint32_t *u, uint32_t *r)
+{
+    bool need[N];
+    bool any = false;
+    if (S.H > 0) {
+        uint32_t e[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t x = (int32_t)u[j] < S.H ? u[j] : 0u;
+            e[j] = S.w8    ? (uint32_t)lds8_ptr(S.ld)[x]
+                   : S.w16 ? (uint32_t)lds16_ptr(S.ld)[x]
+                           : lds_ptr(S.ld)[x];
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const bool in = (int32_t)u[j] < S.H;
+            if (S.w8) {
+                need[j] = !in || e[j] == LDS8_FAR;
+                r[j] = e[j] == 0u ? 0u : e[j] == LDS8_INF ? BC_INF : S.base8 + e[j] - 1u;
+            } else if (S.w16) {
+                need[j] = !in || e[j] == LDS16_FAR;
+                r[j] = e[j] == LDS16_INF ? BC_INF : e[j];
+            } else {
+                need[j] = !in;
+                r[j] = e[j];
+            }
+            any |= need[j];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            need[j] = any = true;
+    }
+    if (__ballot(any)) {
+        uint32_t g[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            g[j] = S.d[need[j] ? u[j] : 0u];
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            r[j] = need[j] ? g[j] : r[j];
+    }
+}
+
 // Single-thread store of a distance (no concurrent access to the entry's word).
 __device__ __forceinline__ void dist_set(const Slab &S, uint32_t u, uint32_t v)
 {
@@ -246,8 +294,7 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x)
     return x;
 }
 
-// Inclusive prefix sums over the lanes, and the OR of all lanes (uniform), by
-// DPP row shifts and row broadcasts.
+// Inclusive prefix sums over the lanes, by DPP row shifts and row broadcasts.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t dpp_or_zero(uint32_t x)
 {
@@ -263,22 +310,6 @@ __device__ __forceinline__ uint32_t wave_incl_sum_u32(uint32_t x)
     x += dpp_or_zero<0x142, 0xa>(x); // row_bcast:15
     x += dpp_or_zero<0x143, 0xc>(x); // row_bcast:31
     return x;
-}
-
-__device__ __forceinline__ uint32_t wave_or_u32(uint32_t x)
-{
-    x |= dpp_or_zero<0x111, 0xf>(x);
-    x |= dpp_or_zero<0x112, 0xf>(x);
-    x |= dpp_or_zero<0x114, 0xf>(x);
-    x |= dpp_or_zero<0x118, 0xf>(x);
-    x |= dpp_or_zero<0x142, 0xa>(x);
-    x |= dpp_or_zero<0x143, 0xc>(x);
-    return (uint32_t)__builtin_amdgcn_readlane((int)x, WAVE - 1);
-}
-
-__device__ __forceinline__ uint64_t wave_or_u64(uint64_t x)
-{
-    return (uint64_t)wave_or_u32((uint32_t)(x >> 32)) << 32 | wave_or_u32((uint32_t)x);
 }
 
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x)

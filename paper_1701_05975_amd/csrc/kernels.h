@@ -68,6 +68,9 @@ struct PlainArgs {
     unsigned long long *err;
 };
 
+// LDS of a batched workgroup besides the resident distances (its control block)
+#define BATCHED_LDS_CTL 3072
+
 hipError_t launch_batched(const BatchArgs &a, bool packed, int nt, bool atomic_bc, int nslabs,
                           hipStream_t st);
 int batched_blocks_per_cu_lds(bool packed, int nt, bool atomic_bc, int lds_bits, size_t lds_bytes);

@@ -34,6 +34,7 @@ __device__ __forceinline__ uint32_t sat_add_u32(uint32_t x, uint64_t y)
 }
 
 struct WgCtl {
+    uint32_t marks[1024 / WAVE][2 * EXPAND_UNROLL]; // flat_starts, per wave
     int near_len, next_cnt, order_cnt, far_cnt, kept_cnt;
     int fin_cnt[3], pend_cnt[3]; // count rounds, each in turn
     int outer_cnt, okept_cnt, resplit;
@@ -57,6 +58,8 @@ struct WgCtl {
     int32_t bcur;
     int bnext, forced, overflowed; // overflowed: a bucket was full in this source
 };
+
+static_assert(sizeof(WgCtl) <= BATCHED_LDS_CTL, "the LDS plan leaves room for WgCtl");
 
 // Phase timing of one workgroup: thread 0 reads the constant-rate device
 // clock at phase boundaries (phases: 0 init, 1 expansion, 2 counts,
@@ -236,6 +239,12 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
     return true;
 }
 
+// The wave's index in its workgroup, in a scalar register.
+__device__ __forceinline__ int wave_index()
+{
+    return __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+}
+
 // Counts the members order[b0, b1) of one band in rounds and leaves them in
 // order[] level by level.  The first round's final vertices go to `fin` (free
 // until the next pile scan) and are copied over the members it read while the
@@ -259,8 +268,9 @@ __device__ __forceinline__ bool wg_count_rounds(const DevGraph &g, const Slab &S
         CountCtx cc;
         cc.items = items;
         cc.len = len;
-        cc.worker = tid / WAVE;
+        cc.worker = wave_index();
         cc.nworkers = NT / WAVE;
+        cc.marks = C.marks[cc.worker];
         cc.lane_max = a.lane_max;
         cc.src_idx = idx;
         cc.base = base;
@@ -495,8 +505,9 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 ec.all_vertices = a.node_parallel;
                 ec.cur_tag = C.gen;
                 ec.vw = a.vw;
-                ec.worker = tid / WAVE;
+                ec.worker = wave_index();
                 ec.nworkers = NT / WAVE;
+                ec.marks = C.marks[ec.worker];
                 ec.thr = C.thr;
                 ec.tag_next = C.gen + 1;
                 ec.band_gen = C.band_gen;
@@ -620,7 +631,7 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 OuterSplitCtx op;
                 op.outer_in = C.ocur ? S.ob : S.oa;
                 op.len = C.outer_cnt;
-                op.worker = tid / WAVE;
+                op.worker = wave_index();
                 op.nworkers = NT / WAVE;
                 op.bound_old = C.bound_old;
                 op.bound = C.bound;
@@ -644,7 +655,7 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 SplitCtx sp;
                 sp.far_in = C.fcur ? S.fb : S.fa;
                 sp.len = C.far_cnt;
-                sp.worker = tid / WAVE;
+                sp.worker = wave_index();
                 sp.nworkers = NT / WAVE;
                 sp.thr_old = C.thr_old;
                 sp.thr = C.thr;
@@ -682,8 +693,9 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                     PushCtx pc;
                     pc.items = S.order + lo;
                     pc.len = hi - lo;
-                    pc.worker = tid / WAVE;
+                    pc.worker = wave_index();
                     pc.nworkers = NT / WAVE;
+                    pc.marks = C.marks[pc.worker];
                     pc.ebc = a.ebc;
                     pc.emap = a.emap;
                     push_level<PACKED, WG_SCOPE>(g, S, pc);
@@ -917,11 +929,14 @@ __global__ __launch_bounds__(256) void k_plain_step(PlainArgs a)
         return;
     const DevGraph &g = a.g;
     Slab S = slab_at(a.slab_base, a.L, 0);
-    const int worker = (int)((blockIdx.x * blockDim.x + threadIdx.x) / WAVE);
+    const int worker =
+        __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) / WAVE));
     const int nworkers = (int)(gridDim.x * blockDim.x / WAVE);
     const int lane = lane_id();
+    __shared__ uint32_t marks[256 / WAVE][2 * EXPAND_UNROLL];
     if (phase == PH_EXPAND) {
         ExpandCtx ec;
+        ec.marks = marks[worker % (256 / WAVE)];
         ec.items = c->cur ? S.qb : S.qa;
         ec.len = c->near_len;
         ec.all_vertices = 0;
@@ -1234,7 +1249,8 @@ __global__ void k_dynamic_apply(double *bc, const double *before, const double *
 size_t batched_lds_bytes(int H, int lb)
 {
     const int per = 32 / lb;
-    return (size_t)((H + per - 1) / per + (H + 31) / 32) * 4; // entries, then one bit each
+    // entries, then one bit each; entry 0 is read for vertices that have none
+    return (size_t)std::max((H + per - 1) / per + (H + 31) / 32, 1) * 4;
 }
 
 template <bool PACKED, int NT, bool ATOMIC, int LB, bool BKT>

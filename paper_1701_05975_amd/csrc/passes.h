@@ -144,6 +144,15 @@ __device__ __forceinline__ void store_f64(double *p, double v)
 // which is only scanned when the threshold passes the bound.  What is the
 // first time follows from the value that the minimum replaced.
 // ---------------------------------------------------------------------------
+// Steps of 64 arcs whose loads are in flight together: with a lane's load
+// behind a branch the compiler waits for it there, and the steps' latencies
+// added up.  1024 sources of R-MAT scale 20: 262 ms at one step, 235 at two, 225
+// at four, 223 at six; a Kronecker graph of scale 16 (1024 threads) 6.4 / 6.5
+// / 6.9 ms at two, four and six, the grid 87 / 88 / 88.
+#ifndef EXPAND_UNROLL
+#define EXPAND_UNROLL 4
+#endif
+
 struct ExpandCtx {
     const int32_t *items;
     int len;
@@ -151,6 +160,7 @@ struct ExpandCtx {
     int32_t cur_tag;      // tag of the queue being expanded (node-parallel filter)
     int vw;               // 0: lane or wave by degree; else a fixed group of vw lanes
     int worker, nworkers; // wave index and wave count over the item list
+    uint32_t *marks;      // 2 EXPAND_UNROLL words of LDS of this wave (flat_starts)
     uint32_t thr;         // band threshold: d < thr is near
     int32_t tag_next;     // tag of the queue being filled
     int32_t band_gen;     // tag of the band's first queue
@@ -331,12 +341,6 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
     }
 }
 
-// Steps of 64 arcs whose loads are in flight together (1 to 4 measure within
-// 2% of each other on every workload: the commits bound the pass).
-#ifndef EXPAND_UNROLL
-#define EXPAND_UNROLL 2
-#endif
-
 // Fixed virtual-warp mapping (Sec. 3.4): a group of vw lanes per vertex,
 // striding over its arcs; vw = 1 is one thread per vertex, vw = 64 one wave.
 template <bool PACKED, int SCOPE, bool BKT = false>
@@ -435,15 +439,39 @@ __device__ __forceinline__ void cand_flush(const Slab &S, const ExpandCtx &c, Ca
     b.cnt = 0;
 }
 
-// The item whose range holds flat position q0 + lane: items 0 .. items-1
-// start at the strictly increasing offsets `off` (each lane its own item's).
-__device__ __forceinline__ int flat_item(uint32_t off, int items, uint32_t q0)
+// Flat layout: items 0 .. items-1 (one per lane, the first lanes) hold the
+// flat positions from the strictly increasing offsets `off` on.  starts[j] gets
+// the positions in [q0 + 64 j, q0 + 64 j + 64) where an item starts (uniform),
+// the result is the number of items that start before q0.  `marks` is 2 N
+// words of LDS of this wave (an OR over the lanes by DPP takes about 30
+// instructions per 64 positions, which showed in the expansion).
+template <int N>
+__device__ __forceinline__ int flat_starts(uint32_t *marks, uint32_t off, int items, uint32_t q0,
+                                           uint64_t *starts)
 {
     const int lane = lane_id();
-    const uint64_t starts =
-        wave_or_u64(lane < items && off >= q0 && off - q0 < WAVE ? 1ull << (off - q0) : 0ull);
-    const int before = __popcll(__ballot(lane < items && off < q0));
-    return before + (int)lanes_below(starts) + (int)((starts >> lane) & 1) - 1;
+    lds_u32 *m = lds_ptr(marks);
+    if (lane < 2 * N)
+        __hip_atomic_store(m + lane, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_wave_barrier();
+    if (lane < items && off >= q0 && off - q0 < WAVE * N)
+        __hip_atomic_fetch_or(m + ((off - q0) >> 5), 1u << ((off - q0) & 31u), __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t w = __hip_atomic_load(m + (lane < 2 * N ? lane : 0), __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        starts[j] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)w, 2 * j + 1) << 32 |
+                    (uint32_t)__builtin_amdgcn_readlane((int)w, 2 * j);
+    return __popcll(__ballot(lane < items && off < q0));
+}
+
+// The item of this lane's position, given the starts in its 64 positions and
+// the number of items that start before them.
+__device__ __forceinline__ int flat_item(uint64_t starts, int before)
+{
+    return before + (int)lanes_below(starts) + (int)((starts >> lane_id()) & 1) - 1;
 }
 
 // The lanes with `have` first, in order (a permutation of the wave); the
@@ -519,34 +547,48 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
         const uint32_t off = incl - deg; // strictly increasing over the items
         const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
         const uint32_t shift = beg - off; // arc position of flat position p: p + shift
+        const uint32_t last =
+            total - 1u + (uint32_t)__builtin_amdgcn_readlane((int)shift, items > 0 ? items - 1 : 0);
+        constexpr int U = EXPAND_UNROLL;
         for (uint32_t p0 = p_first; p0 < total; p0 += p_stride) {
-            uint32_t u[EXPAND_UNROLL], nd[EXPAND_UNROLL], tl[EXPAND_UNROLL];
-            bool ok[EXPAND_UNROLL];
+            uint32_t u[U], nd[U], tl[U], wd[U], du[U];
+            bool ok[U];
+            const int steps = (int)((total - p0 + WAVE - 1) / WAVE); // uniform
+            uint64_t starts[U];
+            int before = flat_starts<U>(c.marks, off, items, p0, starts);
+            // positions past the end read the last arc: no load sits behind a
+            // lane's branch, so the steps' loads overlap
 #pragma unroll
-            for (int j = 0; j < EXPAND_UNROLL; ++j) {
-                const uint32_t q0 = p0 + WAVE * j, p = q0 + lane;
-                const int it = flat_item(off, items, q0);
-                const uint32_t sh = (uint32_t)__shfl((int)shift, it);
-                const uint32_t d = (uint32_t)__shfl((int)dv, it);
-                tl[j] = (uint32_t)__shfl(v, it);
+            for (int j = 0; j < U; ++j) {
+                const uint32_t p = p0 + WAVE * j + lane;
+                u[j] = nd[j] = tl[j] = wd[j] = du[j] = 0;
                 ok[j] = p < total;
-                u[j] = 0;
-                nd[j] = 0;
-                if (ok[j]) {
-                    uint32_t w;
-                    arc_at<PACKED>(g.arc, g.wt, p + sh, g.wshift, g.wmask, u[j], w);
-                    nd[j] = d + w;
+                if (j < steps) {
+                    const int it = flat_item(starts[j], before);
+                    before += __popcll(starts[j]);
+                    const uint32_t sh = (uint32_t)__shfl((int)shift, it);
+                    nd[j] = (uint32_t)__shfl((int)dv, it);
+                    tl[j] = (uint32_t)__shfl(v, it);
+                    wd[j] = g.arc[ok[j] ? p + sh : last];
+                    if (!PACKED)
+                        du[j] = (uint32_t)g.wt[ok[j] ? p + sh : last];
                 }
             }
 #pragma unroll
-            for (int j = 0; j < EXPAND_UNROLL; ++j)
-                ok[j] = ok[j] && nd[j] <= dist_peek(S, u[j]);
+            for (int j = 0; j < U; ++j) {
+                u[j] = PACKED ? wd[j] >> g.wshift : wd[j];
+                nd[j] += PACKED ? (wd[j] & g.wmask) + 1u : du[j];
+            }
+            dist_peek_n<U>(S, u, du);
+#pragma unroll
+            for (int j = 0; j < U; ++j)
+                ok[j] = ok[j] && nd[j] <= du[j];
             // one copy of the commit code for every j
 #pragma nounroll
-            for (int j = 0; j < EXPAND_UNROLL; ++j) {
+            for (int j = 0; j < U && j < steps; ++j) {
                 cand_add<SCOPE, BKT>(S, c, b, ok[0], u[0], nd[0], tl[0], far_min, outer_min, nimp);
 #pragma unroll
-                for (int i = 0; i + 1 < EXPAND_UNROLL; ++i) {
+                for (int i = 0; i + 1 < U; ++i) {
                     ok[i] = ok[i + 1];
                     u[i] = u[i + 1];
                     nd[i] = nd[i + 1];
@@ -1020,6 +1062,7 @@ struct CountCtx {
     const int32_t *items;
     int len;
     int worker, nworkers;
+    uint32_t *marks;      // 2 words of LDS of this wave
     int lane_max;         // lists up to this long are summed by one lane, longer by the wave
     long long src_idx;    // index in the source list (error reports)
     int32_t base, cur;    // round numbers: the source's own level, this round
@@ -1148,7 +1191,9 @@ __device__ __forceinline__ void count_pass(const DevGraph &g, const Slab &S, con
             const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
             uint32_t m = 0; // tight arcs of the lane's item so far
             for (uint32_t q0 = 0; q0 < total; q0 += WAVE) {
-                const int it = flat_item(off, items, q0);
+                uint64_t starts;
+                const int before = flat_starts<1>(c.marks, off, items, q0, &starts);
+                const int it = flat_item(starts, before);
                 const uint32_t p = q0 + lane;
                 const uint32_t ib = (uint32_t)__shfl((int)sb, it);
                 const uint32_t io = (uint32_t)__shfl((int)off, it);
@@ -1244,6 +1289,7 @@ struct PushCtx {
     const int32_t *items;
     int len;
     int worker, nworkers;
+    uint32_t *marks;      // 2 words of LDS of this wave
     double *ebc;          // optional edge betweenness (caller arc order; lists hold positions)
     const uint32_t *emap; // in-row position -> caller arc index
 };
@@ -1288,7 +1334,9 @@ __device__ __forceinline__ void push_level(const DevGraph &g, const Slab &S, con
             const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
             const uint32_t shift = sb - off;
             for (uint32_t q0 = 0; q0 < total; q0 += WAVE) {
-                const int it = flat_item(off, items, q0);
+                uint64_t starts;
+                const int before = flat_starts<1>(c.marks, off, items, q0, &starts);
+                const int it = flat_item(starts, before);
                 const uint32_t p = q0 + lane;
                 const uint32_t sh = (uint32_t)__shfl((int)shift, it);
                 const int src = __shfl(from, it);
