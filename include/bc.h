@@ -165,8 +165,8 @@ typedef struct {
     int32_t lane_max_deg; /* count pass: at most this many recorded predecessors are summed
                              by one lane, more by a whole 64-lane wave (plain form: in-arcs,
                              and out-arcs in the dependency pass) */
-    int32_t wg_threads;   /* batched: threads per workgroup (256, 512 or 1024); with batch
-                             set, a CU's LDS is shared only by the workgroups those
+    int32_t wg_threads;   /* batched: threads per workgroup (256, 512 or 1024; 0 = by graph and
+                             number of sources); with batch set, a CU's LDS is shared only by the workgroups those
                              sources need */
     int32_t autotune;     /* 1 = time candidate settings once per graph and keep the best:
                              band width, workgroup size, dependency method, lane_max_deg,

@@ -557,6 +557,28 @@ int default_delta(const bc_graph *g)
 }
 
 
+// Threads per workgroup when the caller leaves them open.  A workgroup of
+// 1024 threads has a CU to itself, with all of its LDS for distances; smaller
+// ones leave most of the CU idle while there is a source per CU or fewer, and
+// beyond that four sources of 256 threads share the atomic rate and the LDS
+// that one of 1024 uses.  Measured (ms, 256 / 512 / 1024 threads): ER 10k, 64
+// sources 1.11 / 0.70 / 0.56, 4096 sources 12.6 / 10.3 / 9.0; Barabasi-Albert
+// 100k, 16 sources 15.3 / 8.8 / 5.5, 1024 sources 64 / 54 / 46.
+// Two exceptions: small graphs, whose frontiers do not fill 1024 threads (ER
+// 1000, 16 sources 0.25 / 0.22 / 0.22, all sources 0.49 / 0.56 / 0.80), and
+// graphs of at most 8 arcs a vertex, grids above all, whose frontiers stay
+// narrow at any size: more sources than CUs then run side by side (100 x 100
+// grid, 1024 sources 3.3 / 4.5 / 7.9; 300 x 300 grid, 512 sources 17.5 / 15.6 /
+// 21.3).
+int default_wg_threads(const bc_graph *g, int64_t k)
+{
+    if (g->n <= 2048)
+        return k <= g->num_cus / 4 ? 512 : 256;
+    if (k <= g->num_cus || g->maxdeg > 8)
+        return 1024;
+    return k <= 2 * (int64_t)g->num_cus ? 512 : 256;
+}
+
 int lds_bits_for(const bc_graph *g, int requested)
 {
     if (requested == 8)
@@ -641,7 +663,7 @@ ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k)
         throw bc_error(BC_E_INVAL, "far_buckets must be 0, 1 or 2");
     r.mode = o.mode == BC_MODE_PLAIN || o.mode == BC_MODE_INTERLEAVED ? o.mode : BC_MODE_BATCHED;
     r.stream = o.stream ? (hipStream_t)o.stream : g->stream;
-    r.wg_threads = o.wg_threads ? o.wg_threads : 256;
+    r.wg_threads = o.wg_threads ? o.wg_threads : default_wg_threads(g, k);
     if (r.wg_threads != 256 && r.wg_threads != 512 && r.wg_threads != 1024)
         throw bc_error(BC_E_INVAL, "wg_threads must be 256, 512 or 1024");
     r.delta = o.delta ? o.delta : default_delta(g);

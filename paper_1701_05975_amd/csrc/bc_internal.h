@@ -159,6 +159,8 @@ struct bc_result {
 
 SlabLayout slab_layout(int32_t n, int64_t pred_slots);
 int default_delta(const bc_graph *g);
+// Threads per workgroup for k sources when the caller leaves them open.
+int default_wg_threads(const bc_graph *g, int64_t k);
 // Width of the LDS distance entries for a requested width (0 = by graph).
 int lds_bits_for(const bc_graph *g, int requested);
 // LDS-resident distances per source and the matching workgroups per CU.

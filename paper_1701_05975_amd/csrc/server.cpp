@@ -344,7 +344,8 @@ class HipExec {
     {
         if (opts_.compute.wg_threads)
             return opts_.compute.wg_threads;
-        return g->tuned.valid ? g->tuned.wg_threads : 256;
+        // requests keep the GPU full together: the choice for many sources
+        return g->tuned.valid ? g->tuned.wg_threads : default_wg_threads(g, INT64_MAX);
     }
 
     // Creates the graph's sweep contexts; on failure (not enough device
