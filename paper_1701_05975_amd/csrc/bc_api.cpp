@@ -635,7 +635,34 @@ int64_t batch_cap(bc_graph *g)
     return std::min<int64_t>(by_mem, 65535);
 }
 
-ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k)
+// Workgroups per source of the team form (team.hip); 1: one workgroup per
+// source.  A team gives up the distances in LDS and pays a barrier of 2 to 8 us
+// per step, so it needs enough arcs per source and enough members.  Measured, ms
+// with one workgroup / with the team (members): Barabasi-Albert 1M, 10M arcs: 1
+// source 51.7 / 7.0 (32), 16 sources 72 / 15.8 (16), 64 sources 98.7 / 51.8 (4);
+// R-MAT scale 20: 1 source 40.6 / 11.5 (32), 48 sources 62 / 41.7 (5), 64 sources
+// 67.8 / 52 (4), 128 sources 81 / 101 (2: not used); Barabasi-Albert 100k, 1M
+// arcs: 1 source 4.2 / 1.6 (32), 16 sources 4.4 / 2.6 (8), 64 sources 5.3 / 5.8
+// (4: not used); ER 40k, 320k arcs: 1 source 1.17 / 0.86 (16), 16 sources 1.32 /
+// 1.30 (4: not used).  Graphs of at most 8 arcs a vertex (grids) have frontiers
+// that one workgroup handles: 300 x 300 grid, 1 source 7.3 / 14.2 (4).
+static int team_size(const bc_graph *g, const bc_options &o, int64_t k)
+{
+    const bool open = o.wg_threads == 0 && o.lds_vertices == 0 && o.lds_bits == 0 &&
+                      o.virtual_warp == 0 && o.node_parallel == 0 && o.far_buckets == 0 &&
+                      o.dep_mode != 2 && o.accumulate == 0 && !o.autotune &&
+                      (o.batch == 0 || o.batch >= k);
+    const int64_t work = g->nnz + g->n;
+    if (!open || k < 1 || g->maxdeg <= 8 || work < 300000)
+        return 1;
+    // the smaller graphs keep half of the GPU free of barriers
+    const int64_t large = work >= 4000000;
+    const int64_t w = std::min<int64_t>(g->num_cus / (large ? 1 : 2) / k, work < 1000000 ? 16 : 32);
+    const int64_t least = large ? 4 : work < 1000000 ? 16 : 8;
+    return w >= least ? (int)w : 1;
+}
+
+ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k, bool teams)
 {
     ResolvedOptions r;
     bc_options o;
@@ -693,6 +720,17 @@ ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k)
     b = std::min<int64_t>(b, batch_cap(g));
     r.batch = (int)std::max<int64_t>(b, 1);
     r.autotune = o.autotune;
+    if (teams && r.mode == BC_MODE_BATCHED)
+        r.team = team_size(g, o, k);
+    if (r.team > 1) {
+        // a source per team, distances in the slab, one far pile, output by atomics
+        r.batch = (int)std::min<int64_t>(k, batch_cap(g));
+        r.wg_threads = TEAM_THREADS;
+        r.lds_vertices = 0;
+        r.lds_bits = 32;
+        r.far_buckets = 2;
+        r.accumulate = 2;
+    }
     return r;
 }
 
@@ -827,7 +865,17 @@ void launch_batched_pass(bc_graph *g, const ResolvedOptions &r, const int32_t *s
     a.bcap = (int32_t)std::min<size_t>((L.bx + 8 * (size_t)g->n - L.fa) / 4 / (size_t)a.nbk,
                                        (size_t)INT32_MAX);
     hip_check(hipEventRecord(g->ev_k0, st), "event");
-    hip_check(launch_batched(a, g->packed, r.wg_threads, atomic_bc, nslabs, st), "batched kernel");
+    if (r.team > 1) {
+        TeamArgs t;
+        t.b = a;
+        t.ctl = (TeamCtl *)g->team_ctl.p;
+        t.teams = nslabs;
+        t.size = r.team;
+        hip_check(launch_team(t, g->packed, st), "team kernel");
+    } else {
+        hip_check(launch_batched(a, g->packed, r.wg_threads, atomic_bc, nslabs, st),
+                  "batched kernel");
+    }
     hip_check(hipEventRecord(g->ev_k1, st), "event");
     if (!atomic_bc)
         hip_check(launch_reduce_partials(slab_base, L, nslabs, g->n, bc_dev, a.perm, st),
@@ -839,6 +887,8 @@ void run_batched(bc_graph *g, const ResolvedOptions &r, const int32_t *src_dev, 
 {
     hipStream_t st = r.stream;
     ensure_slabs(g, g->batched, r.batch, st);
+    if (r.team > 1 && g->team_ctl.bytes < sizeof(TeamCtl) * (size_t)r.batch)
+        g->team_ctl.alloc(sizeof(TeamCtl) * (size_t)r.batch);
     reset_device_counters(g, st);
     const bool atomic_bc = r.accumulate == 2;
     if (atomic_bc || k == 0)

@@ -86,6 +86,7 @@ struct ResolvedOptions {
     int wg_deg = BC_HUB_DEG;        // expansion: the whole workgroup above this (batched form)
     int node_parallel = 0;
     int far_buckets = 0;  // batched: 0 auto, 1 far-bucket ring, 2 two-tier pile
+    int team = 1;         // batched: workgroups per source (more than 1: the team form)
     int il_groups = 0;    // interleaved form: groups of 64 sources per sweep (0 = by memory)
     hipStream_t stream = nullptr;
 };
@@ -124,6 +125,7 @@ struct bc_graph {
     std::vector<int32_t> host_iperm;
     DevBuf ctl;             // DevCounters
     DevBuf plain_ctl;       // PlainCtl
+    DevBuf team_ctl;        // TeamCtl of each team
     DevBuf src_buf;         // uploaded source lists
     DevCounters *host_counters = nullptr;
     PlainCtl *host_plain = nullptr;
@@ -168,7 +170,8 @@ int lds_bits_for(const bc_graph *g, int requested);
 // than those need share a CU's LDS.
 void batched_lds_plan(const bc_graph *g, int nt, bool atomic_bc, int requested, int bits,
                       int &H, int &per_cu, int64_t want_slabs = 0);
-ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k);
+// teams: whether short source lists may run several workgroups per source.
+ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k, bool teams = true);
 // Most state slabs a batched launch may use (60% of the free device memory,
 // at most 65535).
 int64_t batch_cap(bc_graph *g);

@@ -264,6 +264,18 @@ __device__ __forceinline__ void qbit_clear(const Slab &S, uint32_t u)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
+// The wave's index in its workgroup, in a scalar register.
+__device__ __forceinline__ int wave_index()
+{
+    return __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+}
+
+__device__ __forceinline__ uint32_t sat_add_u32(uint32_t x, uint64_t y)
+{
+    const uint64_t t = (uint64_t)x + y;
+    return t > BC_INF ? BC_INF : (uint32_t)t;
+}
+
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),

@@ -37,6 +37,30 @@ struct BatchArgs {
     int32_t buckets = 0, nbk = 0, bcap = 0;
 };
 
+// Team form: the shared words of one team (device memory, zeroed before each
+// launch).
+enum { TEAM_NEAR, TEAM_MEMBER, TEAM_PEND, TEAM_FINAL, TEAM_HUB, TEAM_STEP_WORDS };
+#define TEAM_HUBS 256
+struct TeamCtl {
+    alignas(128) unsigned int joined; // workgroups that asked to join, and TEAM_CLOSED
+    unsigned int members;             // set once, by the first member
+    unsigned int failed;
+    alignas(128) unsigned int arrived; // barrier arrivals so far
+    alignas(128) long long src[2];     // source index, two sources in turn
+    alignas(128) int step[3][8];       // entries appended in a barrier interval (TEAM_NEAR
+                                       // ...), three intervals in turn
+    int far_cnt[3];                            // per band, three in turn
+    unsigned int far_min[3];
+    alignas(128) int32_t hub_q[TEAM_HUBS];
+};
+
+struct TeamArgs {
+    BatchArgs b;
+    TeamCtl *ctl; // one per team
+    int teams;    // team t owns state slab t
+    int size;     // most workgroups of a team
+};
+
 // Phase machine of the plain form (device memory, one per graph).
 struct PlainCtl {
     int phase;
@@ -73,6 +97,9 @@ struct PlainArgs {
 
 hipError_t launch_batched(const BatchArgs &a, bool packed, int nt, bool atomic_bc, int nslabs,
                           hipStream_t st);
+// teams * size workgroups of TEAM_THREADS; clears a.ctl first
+#define TEAM_THREADS 1024
+hipError_t launch_team(const TeamArgs &a, bool packed, hipStream_t st);
 int batched_blocks_per_cu_lds(bool packed, int nt, bool atomic_bc, int lds_bits, size_t lds_bytes);
 int batched_blocks_per_cu(bool packed, int nt, bool atomic_bc, int lds_bits);
 // dynamic LDS of a batched launch: H resident distances of lds_bits each, and a

@@ -27,12 +27,6 @@
 #define OUTER_BANDS 16
 #endif
 
-__device__ __forceinline__ uint32_t sat_add_u32(uint32_t x, uint64_t y)
-{
-    const uint64_t t = (uint64_t)x + y;
-    return t > BC_INF ? BC_INF : (uint32_t)t;
-}
-
 struct WgCtl {
     uint32_t marks[1024 / WAVE][2 * EXPAND_UNROLL]; // flat_starts, per wave
     int near_len, next_cnt, order_cnt, far_cnt, kept_cnt;
@@ -237,12 +231,6 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
         C.bcnt[slot] = 0;
     __syncthreads();
     return true;
-}
-
-// The wave's index in its workgroup, in a scalar register.
-__device__ __forceinline__ int wave_index()
-{
-    return __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
 }
 
 // Counts the members order[b0, b1) of one band in rounds and leaves them in

@@ -57,7 +57,7 @@ void compute_noalloc(bc_graph *g, const int32_t *src_dev, int64_t k, const bc_op
         throw bc_error(BC_E_INVAL, "the allocation-free entry point runs the batched form only");
     if (opt && opt->autotune)
         throw bc_error(BC_E_INVAL, "the allocation-free entry point does not autotune");
-    ResolvedOptions r = resolve_options(g, opt, k);
+    ResolvedOptions r = resolve_options(g, opt, k, false);
     const SlabLayout L = slab_layout(g->n, g->nnz);
     const int64_t fit = (int64_t)(BC_NOALLOC_SCRATCH_BYTES / std::max<size_t>(L.stride, 1));
     if (fit < 1)

@@ -240,8 +240,7 @@ __device__ __forceinline__ uint64_t *key_ptr(const Slab &S, int32_t v)
 // The list holds EXPAND_WG_CAP vertices; further ones stay with their wave.
 #define EXPAND_WG_CAP 256
 
-// Offers nd to u from tail (lanes with `cand`); every lane of the wave may
-// call it, active lanes together.
+// Offers nd to u from tail (lanes with `cand`); called by whole waves.
 template <int SCOPE, bool BKT = false>
 __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, bool cand,
                                              uint32_t u, uint32_t nd, uint32_t tail,
@@ -324,20 +323,24 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
         }
     }
     if (__ballot(imp)) {
-        int k = wave_alloc(c.next_cnt, pn);
+        // one atomic instruction for all four counters: lane i adds the i-th
+        const uint64_t mn = __ballot(pn), mm = __ballot(pm), mf = __ballot(pf), mo = __ballot(po);
+        const int lane = lane_id();
+        int *const c0 = c.next_cnt, *const c1 = c.order_cnt, *const c2 = c.far_cnt,
+                   *const c3 = c.outer_cnt;
+        int *const at = lane == 0 ? c0 : lane == 1 ? c1 : lane == 2 ? c2 : c3;
+        const int add = __popcll(lane == 0 ? mn : lane == 1 ? mm : lane == 2 ? mf : mo);
+        int base = 0;
+        if (lane < 4 && add > 0)
+            base = atomicAdd(at, add);
         if (pn)
-            c.next_q[k] = (int32_t)u;
-        k = wave_alloc(c.order_cnt, pm);
+            c.next_q[__builtin_amdgcn_readlane(base, 0) + (int)lanes_below(mn)] = (int32_t)u;
         if (pm)
-            c.order[k] = (int32_t)u;
-        k = wave_alloc(c.far_cnt, pf);
+            c.order[__builtin_amdgcn_readlane(base, 1) + (int)lanes_below(mm)] = (int32_t)u;
         if (pf)
-            c.far_q[k] = (int32_t)u;
-        if (__ballot(po)) {
-            k = wave_alloc(c.outer_cnt, po);
-            if (po)
-                c.outer_q[k] = (int32_t)u;
-        }
+            c.far_q[__builtin_amdgcn_readlane(base, 2) + (int)lanes_below(mf)] = (int32_t)u;
+        if (po)
+            c.outer_q[__builtin_amdgcn_readlane(base, 3) + (int)lanes_below(mo)] = (int32_t)u;
     }
 }
 
@@ -368,11 +371,14 @@ __device__ __forceinline__ void expand_pass_vw(const DevGraph &g, const Slab &S,
                 qbit_clear(S, (uint32_t)v);
             dv = dist_get(S, v);
         }
-        for (uint32_t e = beg + sub; e < end; e += W) {
-            uint32_t u, w;
-            arc_at<PACKED>(g.arc, g.wt, e, g.wshift, g.wmask, u, w);
-            relax_commit<SCOPE, BKT>(S, c, dv + w <= dist_peek(S, u), u, dv + w, (uint32_t)v, far_min,
-                                     outer_min, nimp);
+        for (uint32_t e = beg + sub; __ballot(e < end); e += W) { // the whole wave together
+            uint32_t u = 0, w = 0;
+            bool ok = e < end;
+            if (ok) {
+                arc_at<PACKED>(g.arc, g.wt, e, g.wshift, g.wmask, u, w);
+                ok = dv + w <= dist_peek(S, u);
+            }
+            relax_commit<SCOPE, BKT>(S, c, ok, u, dv + w, (uint32_t)v, far_min, outer_min, nimp);
         }
     }
 }
