@@ -217,7 +217,7 @@ typedef struct {
                              bucket; bands are then aligned to multiples of delta.
                              2 = a two-tier pile (values within 16 band widths, then the
                              rest), rescanned at every band change.  0 = the ring when the
-                             maximum weight spans at least 16 band widths, else the pile.
+                             maximum weight spans at least 8 band widths, else the pile.
                              The ring needs head and weight packed in one arc word
                              (bc_graph_info.packed_arcs), fewer than 2^30 vertices and
                              fewer than 2^30 bands up to (n - 1) times the maximum

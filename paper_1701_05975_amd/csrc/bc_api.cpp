@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -545,17 +546,40 @@ static void ensure_sources(bc_graph *g, int64_t k)
 // ---------------------------------------------------------------------------
 // Options
 // ---------------------------------------------------------------------------
-int default_delta(const bc_graph *g)
+// Band width of the near-far split when the caller leaves it open.  Narrow
+// bands improve fewer distances twice (an improvement costs scattered atomics
+// and an expansion), wide ones fill the lanes and need fewer steps, so the best
+// width falls as the graph grows: about as arcs^-0.45, from half the maximum
+// weight up to 80k arcs, and less than half of that where the in-degrees are skewed.
+// Measured best widths / those of this rule (maximum weight 100, 1000, 255): ER
+// 10k 50 / 50, 40k 25 / 27, 500k 6-12 / 9; Barabasi-Albert 10k 200 / 181, 100k 50-100
+// / 64; R-MAT scale 14 15-31 / 32, 17 4-7 / 12, 20 2-4 / 5.  Against 4 maximum
+// weights over the average degree at any size: R-MAT scale 20, 256 sources 110 ->
+// 66 ms, Barabasi-Albert 100k, 1024 sources 37.3 -> 28.4, ER 500k, 256 sources 74 ->
+// 62.  Graphs of at most 8 arcs a vertex (grids) have narrow frontiers and long
+// paths, and want whole weights: 32 x 32 grid 8 maximum weights, 100 x 100 2 to 4,
+// 1000 x 1000 0.7 to 1.  A team pays a barrier over several workgroups per step
+// and wants wider bands (Barabasi-Albert 1M 100-200, R-MAT scale 20 7-15, ER 500k
+// 50).  The plain form, which launches every step, keeps the size-independent
+// width.
+int default_delta(const bc_graph *g, int form, int team)
 {
-    // Band width of the near-far split: a few mean arc weights per average
-    // degree (tuned per graph by the autotuner when asked).
-    const double avg = std::max(1.0, g->avg_deg);
-    double d = 4.0 * (double)g->wmax / avg;
+    const double avg = std::max(1.0, g->avg_deg), wmax = (double)g->wmax;
+    double d;
+    if (form == BC_MODE_PLAIN || g->nnz == 0) {
+        d = 4.0 * wmax / avg;
+    } else if (g->maxdeg <= 8) {
+        d = 4.0 * wmax / avg * std::pow(1e6 / (double)g->n, 0.3);
+    } else {
+        d = (g->renumbered ? 0.2 : 0.5) * wmax *
+            std::min(1.0, std::pow((double)g->nnz / 8e4, -0.45));
+        if (team > 1)
+            d *= 5.0;
+    }
     d = std::max(d, 1.0);
     d = std::min(d, (double)INT32_MAX / 4);
     return (int)d;
 }
-
 
 // Threads per workgroup when the caller leaves them open.  A workgroup of
 // 1024 threads has a CU to itself, with all of its LDS for distances; smaller
@@ -693,7 +717,7 @@ ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k, b
     r.wg_threads = o.wg_threads ? o.wg_threads : default_wg_threads(g, k);
     if (r.wg_threads != 256 && r.wg_threads != 512 && r.wg_threads != 1024)
         throw bc_error(BC_E_INVAL, "wg_threads must be 256, 512 or 1024");
-    r.delta = o.delta ? o.delta : default_delta(g);
+    r.delta = o.delta ? o.delta : default_delta(g, r.mode, 1);
     if (r.mode == BC_MODE_INTERLEAVED && !o.delta) {
         // every band of the interleaved form costs a far-list pass and its rounds
         // a read-back each: wide bands (a few maximum weights) pay off there
@@ -730,6 +754,8 @@ ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k, b
         r.lds_bits = 32;
         r.far_buckets = 2;
         r.accumulate = 2;
+        if (!o.delta)
+            r.delta = default_delta(g, r.mode, r.team);
     }
     return r;
 }
@@ -802,14 +828,18 @@ void bucket_plan(const bc_graph *g, const ResolvedOptions &r, int &buckets, int 
 {
     // One bucket per band a far value can lie ahead (a value found in band b is
     // below (b + 1) delta + w_max), plus slack; the ring pays off when the
-    // weights span many bands, where the pile would be rescanned many times.
+    // weights span many bands, where the pile would be rescanned many times:
+    // R-MAT scale 20, 256 sources, 128 / 36 / 17 bands 65.5 / 69.4 / 83.1 ms against
+    // 75.9 / 75.7 / 88.1; Barabasi-Albert 100k, 1024 sources, 20 / 10 / 5 bands
+    // 28.3 / 28.2 / 30.0 against 29.3 / 28.9 / 30.2; ER 10k, 1024 sources, 4 bands 2.25
+    // against 2.24.
     const int64_t spans = ((int64_t)g->wmax + r.delta - 1) / std::max(r.delta, 1);
     nbk = (int)std::min<int64_t>(spans + 2, BC_BUCKETS_MAX);
     // bucket indices are 32-bit, with room for the ring's width beyond the last
     const int64_t last_bucket = (int64_t)std::max(g->n - 1, 0) * g->wmax / std::max(r.delta, 1);
     const bool index_fits = g->n < (1 << 30) && last_bucket < (int64_t)1 << 30;
     buckets = g->packed && index_fits &&
-              (r.far_buckets == 1 || (r.far_buckets == 0 && spans >= 16));
+              (r.far_buckets == 1 || (r.far_buckets == 0 && spans >= 8));
 }
 
 void set_tier_args(const bc_graph *g, int wg_deg, BatchArgs &a)

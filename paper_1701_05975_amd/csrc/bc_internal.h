@@ -160,7 +160,8 @@ struct bc_result {
 };
 
 SlabLayout slab_layout(int32_t n, int64_t pred_slots);
-int default_delta(const bc_graph *g);
+// Band width for an execution form with `team` workgroups per source.
+int default_delta(const bc_graph *g, int form, int team);
 // Threads per workgroup for k sources when the caller leaves them open.
 int default_wg_threads(const bc_graph *g, int64_t k);
 // Width of the LDS distance entries for a requested width (0 = by graph).

@@ -312,7 +312,7 @@ class HipExec {
     {
         if (opts_.compute.delta)
             return opts_.compute.delta;
-        return g->tuned.valid ? g->tuned.delta : default_delta(g);
+        return g->tuned.valid ? g->tuned.delta : default_delta(g, BC_MODE_BATCHED, 1);
     }
     int lane_max_for(bc_graph *g) const
     {
