@@ -431,8 +431,9 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 }
                 if (LB < 32 || v >= S.H)
                     S.d[v] = BC_INF;
-                S.flags[v] = 0; // tie count and flags start clear
-                *key_ptr(S, v) = KEY_NONE; // no predecessor key yet
+                *key_ptr(S, v) = KEY_NONE; // no key, flags or queue tag
+                S.flags[v] = 0;
+                S.stamp[v] = 0;
             };
             const int lim = ps >= 0 ? g.n_act : n;
             for (int v = tid; v < lim; v += NT)

@@ -259,7 +259,9 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
             // A resident vertex's improvements follow one another in LDS, so its
             // last store is nearly always that of the least distance: the count
             // pass compares the two and scans the in-arcs if it is not.  The
-            // others' check would cost a random read, as much as the atomic.
+            // others' check would cost a random read per visit: with plain
+            // stores for them too the 1000 x 1000 grid takes 108 ms, not 87, and
+            // R-MAT scale 20 226 ms, not 213.
             const uint64_t key = (uint64_t)nd << 32 | tail;
             if ((int32_t)u < S.H)
                 __hip_atomic_store(key_ptr(S, (int32_t)u), key, __ATOMIC_RELAXED, SCOPE);
@@ -1130,8 +1132,8 @@ __device__ __forceinline__ void count_pass(const DevGraph &g, const Slab &S, con
         bool scan = false;
         if (valid) {
             v = c.items[i];
-            const int32_t fl = S.flags[v];
             const uint64_t key = *key_ptr(S, v);
+            const int32_t fl = S.flags[v];
             const uint32_t nt = (uint32_t)fl >> TIE_SHIFT;
             // a resident vertex's key is the last one stored: of the final
             // distance, but for a race between two improvements

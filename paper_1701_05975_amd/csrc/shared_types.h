@@ -50,13 +50,15 @@ struct DevGraph {
 // one line instead of one line per field.  Record layout:
 // ---------------------------------------------------------------------------
 #define VREC_BYTES 32
-#define VREC_STAMP 0  // i32 tag of the latest near queue an improvement put the vertex in
-#define VREC_FLAGS 4  // i32 flags, and the count of ties (VFLAG_*, TIE_SHIFT)
-#define VREC_LEVEL 8  // i32 number of the count round the vertex became final in
-#define VREC_PRED1 12 // i32 the only DAG predecessor, or -(m + 1): m of them in preds[]
-#define VREC_SIGMA 16 // u64 shortest-path count (plain form: 0 = not yet final)
-#define VREC_DELTA 24 // f64 dependency (plain form: negative = not yet final); before the
+// (fields that one pass reads or writes together lie in one 16-byte half: a
+// scattered access costs the same at 4 and at 16 bytes)
+#define VREC_LEVEL 0  // i32 number of the count round the vertex became final in
+#define VREC_PRED1 4  // i32 the only DAG predecessor, or -(m + 1): m of them in preds[]
+#define VREC_SIGMA 8  // u64 shortest-path count (plain form: 0 = not yet final)
+#define VREC_DELTA 16 // f64 dependency (plain form: negative = not yet final); before the
                       // vertex is counted its predecessor key (batched form)
+#define VREC_FLAGS 24 // i32 flags, and the count of ties (VFLAG_*, TIE_SHIFT)
+#define VREC_STAMP 28 // i32 tag of the latest near queue an improvement put the vertex in
 
 // Byte offsets of the slab arrays inside one slot (all 256-byte aligned).
 struct SlabLayout {

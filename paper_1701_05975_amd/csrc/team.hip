@@ -193,18 +193,15 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
         for (int v = gtid; v < n; v += gn) {
             const bool is = v == s; // final from the start, a level of its own
             S.d[v] = is ? 0u : BC_INF;
+            *key_ptr(S, v) = is ? 0ull : KEY_NONE; // the source's dependency is 0.0
             S.flags[v] = 0;
-            if (restart) {
-                S.stamp[v] = 0;
+            S.stamp[v] = 0;
+            if (restart)
                 S.level[v] = 0;
-            }
             if (is) {
                 S.level[v] = base;
-                S.sigma[v] = 1;
                 S.pred1[v] = -1;
-                S.delta[v] = 0.0;
-            } else {
-                *key_ptr(S, v) = KEY_NONE;
+                S.sigma[v] = 1;
             }
         }
         if (lead) {
