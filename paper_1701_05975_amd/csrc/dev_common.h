@@ -299,11 +299,14 @@ __device__ __forceinline__ int wave_alloc(int *counter, bool pred)
 
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x)
 {
-    for (int o = 32; o > 0; o >>= 1) {
-        uint32_t y = __shfl_xor(x, o);
-        x = y < x ? y : x;
-    }
-    return x;
+    auto least = [](uint32_t p, int q) { return p < (uint32_t)q ? p : (uint32_t)q; };
+    x = least(x, __builtin_amdgcn_update_dpp(-1, (int)x, 0x111, 0xf, 0xf, false));
+    x = least(x, __builtin_amdgcn_update_dpp(-1, (int)x, 0x112, 0xf, 0xf, false));
+    x = least(x, __builtin_amdgcn_update_dpp(-1, (int)x, 0x114, 0xf, 0xf, false));
+    x = least(x, __builtin_amdgcn_update_dpp(-1, (int)x, 0x118, 0xf, 0xf, false));
+    x = least(x, __builtin_amdgcn_update_dpp(-1, (int)x, 0x142, 0xa, 0xf, false));
+    x = least(x, __builtin_amdgcn_update_dpp(-1, (int)x, 0x143, 0xc, 0xf, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, WAVE - 1);
 }
 
 // Inclusive prefix sums over the lanes, by DPP row shifts and row broadcasts.

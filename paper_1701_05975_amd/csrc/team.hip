@@ -374,9 +374,9 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
 
         // backward pass: the levels in reverse, down to the source's own
         if (ok) {
-            int hi = band_start;
+            int hi = band_start, lo = S.band_off[nlev - 1];
             for (int l = nlev - 1; l > 0 && ok; --l) {
-                const int lo = S.band_off[l];
+                const int below = S.band_off[l - 1];
                 PushCtx pc;
                 pc.items = S.order + lo;
                 pc.len = hi - lo;
@@ -387,6 +387,7 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
                 pc.emap = a.emap;
                 push_level<PACKED, AG_SCOPE>(g, S, pc);
                 hi = lo;
+                lo = below;
                 ok = team_barrier(W, y, par, band);
             }
             drounds += (unsigned long long)(nlev - 1);
