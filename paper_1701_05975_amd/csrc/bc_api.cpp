@@ -756,6 +756,11 @@ ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k, b
         r.accumulate = 2;
         if (!o.delta)
             r.delta = default_delta(g, r.mode, r.team);
+        // the list costs a team a pass and a barrier, and its waves are many:
+        // R-MAT scale 20, 1 source 5.98 ms at BC_HUB_DEG, 5.40 at twice that, 16
+        // sources 15.3 / 14.0; Barabasi-Albert 1M and Kronecker scale 17 the same
+        if (!o.wg_min_deg)
+            r.wg_deg = std::max(r.wave_deg, 2 * BC_HUB_DEG);
     }
     return r;
 }

@@ -40,7 +40,7 @@ struct BatchArgs {
 // Team form: the shared words of one team (device memory, zeroed before each
 // launch).
 enum { TEAM_NEAR, TEAM_MEMBER, TEAM_PEND, TEAM_FINAL, TEAM_HUB, TEAM_STEP_WORDS };
-#define TEAM_HUBS 256
+#define TEAM_HUBS 4096
 struct TeamCtl {
     alignas(128) unsigned int joined; // workgroups that asked to join, and TEAM_CLOSED
     unsigned int members;             // set once, by the first member

@@ -237,8 +237,15 @@ __device__ __forceinline__ uint64_t *key_ptr(const Slab &S, int32_t v)
 // Hubs (batched form): a vertex with more than wg_deg arcs (default
 // BC_HUB_DEG) is expanded by every wave of the workgroup after the pass, so
 // that it does not keep one wave busy while the others wait at the barrier.
-// The list holds EXPAND_WG_CAP vertices; further ones stay with their wave.
+// The list holds EXPAND_WG_CAP vertices (a team's, in global memory,
+// EXPAND_TEAM_CAP); further ones stay with their wave.
 #define EXPAND_WG_CAP 256
+#define EXPAND_TEAM_CAP 4096
+
+template <int SCOPE> constexpr int hub_cap()
+{
+    return SCOPE == __HIP_MEMORY_SCOPE_AGENT ? EXPAND_TEAM_CAP : EXPAND_WG_CAP;
+}
 
 // Offers nd to u from tail (lanes with `cand`); called by whole waves.
 template <int SCOPE, bool BKT = false>
@@ -493,8 +500,15 @@ __device__ __forceinline__ int front_place(uint64_t mask, bool have)
 // Expansion with the arcs of up to 64 queued vertices laid out flat over the
 // lanes (the degree-aware mapping of Sec. 3.4 carried to single arcs: every
 // lane has an arc whatever the degrees are).  `hubs`: the vertices listed in
-// huge_q instead of the queue, each by every wave together.  Called by whole
-// waves; candidates stay in b until cand_flush.
+// huge_q instead of the queue, the flat arcs of 64 of them at a time dealt out
+// over every wave.  Called by whole waves; candidates stay in b until cand_flush.
+// Hubs taken one after another cost a chain of four dependent loads each, which
+// kept a team (its loads miss the L1 after every barrier) at 4 us a hub.
+// Flat, ms before / after: R-MAT scale 17, 1 source 6.5 / 2.0, scale 20, 1
+// source 10.7 / 6.2, 48 sources 40.3 / 36.0; one workgroup per source, Kronecker
+// scale 16, 256 sources 6.49 / 5.74.  A team's list of 256 was often full, and
+// the rest with a wave each: scale 17,
+// 16 sources 3.6 / 3.2 with 4096.
 template <bool PACKED, int SCOPE, bool BKT = false>
 __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, const ExpandCtx &c,
                                             bool hubs, CandBuf &b, uint32_t &far_min,
@@ -505,14 +519,14 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
         return;
     }
     const int lane = lane_id();
-    const int len = hubs                       ? (*c.huge_cnt < EXPAND_WG_CAP ? *c.huge_cnt
-                                                                              : EXPAND_WG_CAP)
+    constexpr int cap = hub_cap<SCOPE>();
+    const int len = hubs             ? (*c.huge_cnt < cap ? *c.huge_cnt : cap)
                     : c.all_vertices ? g.n
                                      : c.len;
     // a short queue is spread over every wave
     int chunk = (len + c.nworkers - 1) / c.nworkers;
-    chunk = hubs ? 1 : chunk < WAVE ? chunk : WAVE;
-    const int first = hubs ? 0 : c.worker * chunk, stride = hubs ? 1 : c.nworkers * chunk;
+    chunk = !hubs && chunk < WAVE ? chunk : WAVE;
+    const int first = hubs ? 0 : c.worker * chunk, stride = hubs ? WAVE : c.nworkers * chunk;
     const uint32_t p_first = hubs ? (uint32_t)c.worker * (WAVE * EXPAND_UNROLL) : 0u;
     const uint32_t p_stride = (hubs ? (uint32_t)c.nworkers : 1u) * (WAVE * EXPAND_UNROLL);
     for (int base = first; base < len; base += stride) {
@@ -536,7 +550,7 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
         if (c.huge_q && !hubs) {
             const bool huge = deg > c.wg_deg;
             const int k = wave_alloc(c.huge_cnt, huge);
-            if (huge && k < EXPAND_WG_CAP) {
+            if (huge && k < cap) {
                 c.huge_q[k] = v;
                 deg = 0;
             }

@@ -24,7 +24,7 @@
 #define TEAM_JOIN_TICKS 2000ll          // 20 us of the 100 MHz device clock
 #define TEAM_WAIT_TICKS (100000000ll * 8) // a barrier that waits 8 s has failed
 
-static_assert(TEAM_HUBS == EXPAND_WG_CAP, "the hub list of a pass");
+static_assert(TEAM_HUBS == EXPAND_TEAM_CAP, "the hub list of a pass");
 
 template <class T> __device__ __forceinline__ T ag_load(const T *p)
 {

@@ -64,6 +64,24 @@ def test_team_matches_oracle(name):
     G.close()
 
 
+@pytest.mark.parametrize("hubs", [1, 63, 64, 65, 4095, 4097])
+def test_team_hub_list(hubs):
+    """A queue with as many hubs as a group of 64, one more and one less, and
+    as the list holds (4096)."""
+    rng = np.random.default_rng(hubs)
+    n, deg, tails = 300_000, 1100, np.arange(1, hubs + 1)
+    src = np.concatenate([np.zeros(hubs, np.int64), np.repeat(tails, deg)])
+    dst = np.concatenate([tails, rng.integers(5000, 8000, hubs * deg)])
+    w = np.concatenate([np.ones(hubs, np.int64), rng.integers(1, 4, hubs * deg)])
+    g = gg.csr_from_arcs(n, src, dst, w, directed=True)
+    G = bc.Graph(g)
+    s = np.array([0, 1], np.int32)
+    got, st = G.bc(s)
+    assert st["lds_vertices"] == 0, st
+    close(got, oracle.oracle_bc(g, s), 1e-11)
+    G.close()
+
+
 def test_team_edges_and_errors():
     torch = pytest.importorskip("torch")
     g = gg.er_graph(40_000, 160_000, 1, 5, seed=65)
