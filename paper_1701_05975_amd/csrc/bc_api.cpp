@@ -906,6 +906,13 @@ void launch_batched_pass(bc_graph *g, const ResolvedOptions &r, const int32_t *s
         t.ctl = (TeamCtl *)g->team_ctl.p;
         t.teams = nslabs;
         t.size = r.team;
+        // the steps of a bound: the window holds an offer of the largest weight
+        // from anywhere in a band
+        t.bounds = (int)std::min<size_t>(((size_t)g->n + 15) / 16 * 16,
+                                         160 * 1024 - TEAM_LDS_CTL);
+        t.bshift = 0;
+        while (((int64_t)(SEEN_WIN - SEEN_REBASE) << t.bshift) < (int64_t)g->wmax + r.delta)
+            ++t.bshift;
         hip_check(launch_team(t, g->packed, st), "team kernel");
     } else {
         hip_check(launch_batched(a, g->packed, r.wg_threads, atomic_bc, nslabs, st),

@@ -54,6 +54,9 @@ struct Slab {
     int32_t w16;       // LDS entries are 16-bit; LDS16_FAR = look in d[]
     int32_t w8;        // LDS entries are 8-bit, relative to base8 (see LDS8_WIN)
     uint32_t base8;    // 8-bit entries: the window's base (a band threshold)
+    uint32_t *seen;    // team form: upper bounds of the distances of vertices 0 .. HB-1,
+    int32_t HB;        // in LDS, one byte each, relative to base8 (see seen_bound)
+    int32_t bshift;    // a byte counts steps of 1 << bshift
     int32_t *preds;    // v's DAG predecessors when it has several, at preds[trow[v] ...]
 };
 
@@ -80,6 +83,9 @@ __device__ __forceinline__ Slab slab_at(char *base, const SlabLayout &L, int slo
     s.w16 = 0;
     s.w8 = 0;
     s.base8 = 0;
+    s.seen = nullptr;
+    s.HB = 0;
+    s.bshift = 0;
     s.preds = (int32_t *)(p + L.preds);
     return s;
 }
@@ -115,6 +121,19 @@ __device__ __forceinline__ lds_u16 *lds16_ptr(uint32_t *p) { return (lds_u16 *)p
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 __device__ __forceinline__ lds_u8 *lds8_ptr(uint32_t *p) { return (lds_u8 *)p; }
+
+// Bounds of the team form: its workgroups share the distances in d[], but a
+// distance only falls, so whatever a workgroup has read or offered stays an
+// upper bound of it, and an offer above the bound needs no look at d[].  Byte
+// e < SEEN_NONE says d[u] <= base8 + (e << bshift); base8 follows the bands
+// (every later offer lies above it).
+
+__device__ __forceinline__ uint32_t seen_code(const Slab &S, uint32_t d)
+{
+    const uint32_t r = (1u << S.bshift) - 1u;
+    const uint32_t e = d <= S.base8 ? 0u : (uint32_t)(((uint64_t)(d - S.base8) + r) >> S.bshift);
+    return e <= SEEN_WIN ? e : SEEN_NONE;
+}
 
 __device__ __forceinline__ uint32_t dist_get(const Slab &S, uint32_t u)
 {
@@ -161,10 +180,43 @@ __device__ __forceinline__ uint32_t dist_peek(const Slab &S, uint32_t u)
 
 // dist_peek of N vertices, without a branch around any load, so that the loads
 // of all N are in flight together: a lane that needs no d[] entry reads the
-// first one, and a wave whose lanes all hold theirs in LDS reads none.
+// first one, and a wave whose lanes all hold theirs in LDS reads none.  nd: the
+// values offered to them (lanes with ok), which are committed before the next
+// barrier if they are no larger than the result.
 template <int N>
-__device__ __forceinline__ void dist_peek_n(const Slab &S, const uint32_t *u, uint32_t *r)
+__device__ __forceinline__ void dist_peek_n(const Slab &S, const uint32_t *u, const uint32_t *nd,
+                                            const bool *ok, uint32_t *r)
 {
+    if (S.HB > 0) {
+        uint32_t e[N], d[N];
+        bool any = false, need[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            e[j] = lds8_ptr(S.seen)[(int32_t)u[j] < S.HB ? u[j] : 0u];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const bool in = (int32_t)u[j] < S.HB && e[j] != SEEN_NONE;
+            r[j] = S.base8 + (e[j] << S.bshift);
+            need[j] = ok[j] && (!in || nd[j] <= r[j]);
+            any |= need[j];
+        }
+        if (__ballot(any)) {
+#pragma unroll
+            for (int j = 0; j < N; ++j)
+                d[j] = S.d[need[j] ? u[j] : 0u];
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                if (need[j]) {
+                    r[j] = d[j];
+                    const uint32_t f = seen_code(S, nd[j] < d[j] ? nd[j] : d[j]);
+                    if ((int32_t)u[j] < S.HB && f < e[j])
+                        lds8_ptr(S.seen)[u[j]] = (uint8_t)f;
+                }
+            }
+        }
+        return;
+    }
+
     bool need[N];
     bool any = false;
     if (S.H > 0) {

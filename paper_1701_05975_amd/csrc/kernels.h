@@ -59,6 +59,8 @@ struct TeamArgs {
     TeamCtl *ctl; // one per team
     int teams;    // team t owns state slab t
     int size;     // most workgroups of a team
+    int bounds;   // vertices with a distance bound in LDS, a multiple of 16
+    int bshift;   // and the unit of the bounds
 };
 
 // Phase machine of the plain form (device memory, one per graph).
@@ -99,6 +101,8 @@ hipError_t launch_batched(const BatchArgs &a, bool packed, int nt, bool atomic_b
                           hipStream_t st);
 // teams * size workgroups of TEAM_THREADS; clears a.ctl first
 #define TEAM_THREADS 1024
+// LDS of a team workgroup besides the bounds
+#define TEAM_LDS_CTL 1024
 hipError_t launch_team(const TeamArgs &a, bool packed, hipStream_t st);
 int batched_blocks_per_cu_lds(bool packed, int nt, bool atomic_bc, int lds_bits, size_t lds_bytes);
 int batched_blocks_per_cu(bool packed, int nt, bool atomic_bc, int lds_bits);

@@ -601,7 +601,7 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
                 u[j] = PACKED ? wd[j] >> g.wshift : wd[j];
                 nd[j] += PACKED ? (wd[j] & g.wmask) + 1u : du[j];
             }
-            dist_peek_n<U>(S, u, du);
+            dist_peek_n<U>(S, u, nd, ok, du);
 #pragma unroll
             for (int j = 0; j < U; ++j)
                 ok[j] = ok[j] && nd[j] <= du[j];

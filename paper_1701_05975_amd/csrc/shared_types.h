@@ -80,3 +80,8 @@ struct DevStats {
     // expansion, count rounds, dependency rounds, far-pile splits
     unsigned long long ticks[5];
 };
+
+// Distance bounds of the team form (one byte each): steps above a base, or none
+#define SEEN_NONE 0xffu
+#define SEEN_WIN 254u
+#define SEEN_REBASE 32u // re-base once the band threshold is this many steps above

@@ -82,6 +82,21 @@ def test_team_hub_list(hubs):
     G.close()
 
 
+@pytest.mark.parametrize("n, m, whi", [(40_000, 160_000, 50_000), (200_000, 400_000, 10_000),
+                                        (200_000, 400_000, 1)])
+def test_team_distance_bounds(n, m, whi):
+    """Bounds with a unit above one and of one, more vertices than have a bound
+    (n = 200,000), arcs that are not packed (n = 40,000)."""
+    g = gg.er_graph(n, m, 1, whi, seed=67)
+    G = bc.Graph(g)
+    for delta in (0, max(whi // 50, 1), 8 * whi):
+        s = gg.sample_sources(g, 3, seed=3)
+        got, st = G.bc(s, delta=delta)
+        assert st["lds_vertices"] == 0, st
+        close(got, oracle.oracle_bc(g, s), 1e-11)
+    G.close()
+
+
 def test_team_edges_and_errors():
     torch = pytest.importorskip("torch")
     g = gg.er_graph(40_000, 160_000, 1, 5, seed=65)
