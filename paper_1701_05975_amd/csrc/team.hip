@@ -122,8 +122,21 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
     if (tid == 0) {
         W.failed = 0;
         W.team = -1;
+        // Consecutive workgroups start on the eight XCDs in turn, and a team inside
+        // one shares its L2: class c holds the teams c, c + 8, ..., and a workgroup
+        // asks the teams class by class, from its own class on.  (blockIdx + i) mod
+        // teams / this, ms: R-MAT scale 20, 7 sources 10.3 / 7.7, 9 sources
+        // 11.5 / 9.1; Barabasi-Albert 1M, 7 sources 10.2 / 8.5; ER 500k, 17 sources 7.7
+        // / 7.0; 8 and 16 teams, in their classes either way, the same.
+        const int classes = ta.teams < 8 ? ta.teams : 8;
+        const int q = ta.teams / classes, more = ta.teams % classes; // the first have q + 1
+        const int own = (int)(blockIdx.x % 8u) % classes;
+        const int at = own * q + (own < more ? own : more) +
+                       (int)(blockIdx.x / 8u) % (own < more ? q + 1 : q);
         for (int i = 0; i < ta.teams && W.team < 0; ++i) {
-            const int t = (int)((blockIdx.x + (unsigned)i) % (unsigned)ta.teams);
+            const int x = (at + i) % ta.teams, y = x - more * (q + 1);
+            const int t = y < 0 ? x / (q + 1) + classes * (x % (q + 1))
+                                : more + y / q + classes * (y % q);
             TeamCtl *c = &ta.ctl[t];
             if (ag_load(&c->joined) >= (unsigned)ta.size) // full or closed
                 continue;
