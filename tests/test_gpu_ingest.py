@@ -157,3 +157,48 @@ def test_device_validation_matches_host_validation():
     h = bc.bc_create_graph_device(a.n, int(col_t.numel()), rp_t.data_ptr(), col_t.data_ptr(),
                                   w_t.data_ptr(), bc.BC_DIRECTED)
     bc.bc_destroy_graph(h)
+
+
+def _undirected_rows(n, pairs, seed, in_order):
+    """CSR of the undirected edges (u, v, w), rows in (head, weight) order or not."""
+    arcs = [(u, v, w) for u, v, w in pairs] + [(v, u, w) for u, v, w in pairs if u != v]
+    key = {a: r for a, r in zip(arcs, np.random.default_rng(seed).permutation(len(arcs)))}
+    arcs.sort(key=(lambda a: a) if in_order else (lambda a: (a[0], key[a])))
+    src, col, w = (np.array(x) for x in zip(*arcs))
+    rp = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int64)
+    return gg.CSRGraph(n, rp, col.astype(np.int32), w.astype(np.int32), directed=False,
+                       m=len(pairs), name="rows")
+
+
+@pytest.mark.parametrize("in_order", [True, False])
+@pytest.mark.parametrize("hub", [1, 40])
+def test_reverse_arcs_of_rows_in_any_order(in_order, hub):
+    """Parallel arcs of equal and of different weights, self-loops, a hub; and
+    the same arrays with one arc changed, which no longer are symmetric."""
+    rng = np.random.default_rng(hub)
+    n = 60
+    pairs = [(int(a), int(b), int(x)) for a, b, x in zip(
+        rng.integers(0, n, 150), rng.integers(0, n, 150), rng.integers(1, 4, 150))]
+    pairs += pairs[:20] + [(0, v, 2) for v in range(1, hub + 1)]
+    g = _undirected_rows(n, pairs, 5, in_order)
+    for keep in (False, True):
+        H = bc.Graph(g, keep_order=keep, edges=True)
+        D = device_graph(g, keep_order=keep, edges=True)
+        assert D.info() == H.info()
+        rel_close(D.bc(None)[0], H.bc(None)[0], 1e-12)
+        rel_close(D.edge_bc(None)[0], H.edge_bc(None)[0], 1e-12)
+        H.close()
+        D.close()
+    for what in ("weight", "head"):
+        col, w = g.col.copy(), g.w.copy()
+        e = int(g.row_ptr[7])  # a row's first arc: the row stays in order
+        if what == "weight":
+            w[e] = 4
+        else:
+            col[e] = 7 if col[e] != 7 else 8
+        b = gg.CSRGraph(n, g.row_ptr, col, w, directed=False, m=g.m, name="x")
+        rp_t, col_t, w_t = tensors(b)
+        hs = _status(lambda: bc.bc_create_graph(b.n, b.row_ptr, b.col, b.w, 0))
+        ds = _status(lambda: bc.bc_create_graph_device(
+            b.n, int(col_t.numel()), rp_t.data_ptr(), col_t.data_ptr(), w_t.data_ptr(), 0))
+        assert hs == ds == bc.BC_E_GRAPH, what
