@@ -1416,8 +1416,8 @@ hipError_t launch_inarc_bound(const uint32_t *trow, int32_t n, int *out, hipStre
     if (e != hipSuccess || n <= 0)
         return e;
     int blocks = (n + 255) / 256;
-    if (blocks > 4096)
-        blocks = 4096;
+    if (blocks > 256) // one atomic a wave, on one word: few waves
+        blocks = 256;
     hipLaunchKernelGGL(k_inarc_bound, dim3(blocks), dim3(256), 0, st, trow, n, out);
     return hipGetLastError();
 }
