@@ -851,6 +851,7 @@ void set_tier_args(const bc_graph *g, int wg_deg, BatchArgs &a)
 {
     a.wg_deg = (uint32_t)wg_deg;
     a.hubs = g->maxdeg > wg_deg;
+    a.narrow = g->maxdeg <= NARROW_DEG && !a.hubs;
 }
 
 void check_device_errors(const DevCounters &c)

@@ -24,6 +24,7 @@ struct BatchArgs {
     int32_t hubs;                 // the graph has vertices of more than wg_deg arcs
     int32_t push;                 // 1: dependencies along the recorded DAG; 0: pulls over out-arcs
     int32_t vw;                   // expansion: 0 adaptive lane/wave, else lanes per vertex
+    int32_t narrow = 0;           // expansion of short queues by small groups (NARROW_DEG)
     int32_t node_parallel;        // expansion scans every vertex instead of the queue
     double *ebc;                  // optional edge betweenness output (caller arc order)
     const uint32_t *emap;         // in-row position -> caller arc index

@@ -499,6 +499,15 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             int32_t gen = __builtin_amdgcn_readfirstlane(C.gen);
             unsigned long long iters = C.iters;
             const bool hubs = a.hubs && !a.vw;
+            // A queue that gives no wave more than 16 vertices of a few arcs each is
+            // one step in any layout, and what counts is the chain before its
+            // commit: groups of NARROW_VW lanes need no prefix sum and no marks.
+            // Flat / groups: 100 x 100 grid, 1 source 1.25 / 1.02 ms, 64 sources 1.51 /
+            // 1.24; 32 x 32, 64 sources 440 / 363 us; 300 x 300, 64 sources 7.7 / 6.8
+            // ms.  Longer queues are faster flat (groups for all of them: 1000 x 1000,
+            // 256 sources 86.6 / 89.3 ms, 300 x 300, 512 sources 15.3 / 16.2), and so
+            // are varying degrees (ER 1000, all sources 432 / 459 us).
+            const int narrow_len = a.narrow && a.vw == 0 && !a.node_parallel ? NT / NARROW_VW : 0;
             ExpandCtx ec;
             ec.all_vertices = a.node_parallel;
             ec.vw = a.vw;
@@ -537,15 +546,20 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 ec.huge_cnt = &C.huge_cnt[slot];
                 uint32_t fmin = BC_INF, omin = BC_INF;
                 CandBuf cb{0u, 0u, 0u, 0};
+                if (near_len <= narrow_len) {
+                    expand_pass_vw<PACKED, WG_SCOPE, BKT>(g, S, ec, NARROW_VW, fmin, omin,
+                                                          st_imp);
+                } else {
 #pragma nounroll
-                for (int part = 0;; ++part) {
-                    expand_pass<PACKED, WG_SCOPE, BKT>(g, S, ec, part == 1, cb, fmin, omin,
-                                                       st_imp);
-                    if (!hubs || part == 1)
-                        break;
-                    __syncthreads(); // the hubs the pass listed, each by the whole workgroup
+                    for (int part = 0;; ++part) {
+                        expand_pass<PACKED, WG_SCOPE, BKT>(g, S, ec, part == 1, cb, fmin, omin,
+                                                           st_imp);
+                        if (!hubs || part == 1)
+                            break;
+                        __syncthreads(); // the hubs the pass listed, by the whole workgroup
+                    }
+                    cand_flush<WG_SCOPE, BKT>(S, ec, cb, fmin, omin, st_imp);
                 }
-                cand_flush<WG_SCOPE, BKT>(S, ec, cb, fmin, omin, st_imp);
                 if (__ballot(fmin != BC_INF)) {
                     fmin = wave_min_u32(fmin);
                     if (lane == 0)

@@ -357,9 +357,8 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
 // striding over its arcs; vw = 1 is one thread per vertex, vw = 64 one wave.
 template <bool PACKED, int SCOPE, bool BKT = false>
 __device__ __forceinline__ void expand_pass_vw(const DevGraph &g, const Slab &S, const ExpandCtx &c,
-                               uint32_t &far_min, uint32_t &outer_min, uint64_t &nimp)
+                               int W, uint32_t &far_min, uint32_t &outer_min, uint64_t &nimp)
 {
-    const int W = c.vw;
     const int groups = WAVE / W;
     const int lane = lane_id(), grp = lane / W, sub = lane % W;
     const int len = c.all_vertices ? g.n : c.len;
@@ -515,7 +514,7 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
                                             uint32_t &outer_min, uint64_t &nimp)
 {
     if (c.vw > 0) {
-        expand_pass_vw<PACKED, SCOPE, BKT>(g, S, c, far_min, outer_min, nimp);
+        expand_pass_vw<PACKED, SCOPE, BKT>(g, S, c, c.vw, far_min, outer_min, nimp);
         return;
     }
     const int lane = lane_id();

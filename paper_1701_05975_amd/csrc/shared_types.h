@@ -13,6 +13,10 @@
 #define BC_DEF_LANE_DEG 8
 #define BC_DEF_WAVE_DEG 64
 #define BC_HUB_DEG 512
+// Graphs of at most NARROW_DEG arcs a vertex (grids): short queues are expanded
+// by groups of NARROW_VW lanes (k_batched)
+#define NARROW_DEG 8
+#define NARROW_VW 4
 // Most buckets of the far-bucket ring (batched form).
 #define BC_BUCKETS_MAX 128
 

@@ -56,3 +56,46 @@ def test_layers(width, degrees):
         od = np.where(od == np.iinfo(np.int64).max, 2**31 - 1, od)
         assert np.array_equal(d, od) and np.array_equal(sg, osg), opts
     G.close()
+
+
+def narrow_layers(width: int, seed: int):
+    """A tree of at most 8 arcs a vertex whose leaves, all queued in one step, are
+    `width`; each leaf has 0 to 8 arcs to a pool, with small weights."""
+    rng = np.random.default_rng(seed)
+    sizes = [width]
+    while sizes[-1] > 1:
+        sizes.append((sizes[-1] + 7) // 8)
+    src, dst, w, first = [], [], [], 0
+    for up, down in zip(sizes[:0:-1], sizes[-2::-1]):
+        src.append(first + np.arange(down) * up // down)
+        dst.append(first + up + np.arange(down))
+        w.append(np.ones(down, np.int64))
+        first += up
+    deg = rng.integers(0, 9, width)
+    pool = width + 9
+    src.append(np.repeat(first + np.arange(width), deg))
+    dst.append(first + width + np.concatenate(
+        [rng.choice(pool, d, replace=False) for d in deg]).astype(np.int64))
+    w.append(rng.integers(1, 4, int(deg.sum())))
+    src.append(first + width + np.arange(pool))
+    dst.append(np.full(pool, first + width + pool))
+    w.append(rng.integers(1, 4, pool))
+    return gg.csr_from_arcs(first + width + pool + 1, np.concatenate(src), np.concatenate(dst),
+                            np.concatenate(w), directed=True)
+
+
+@pytest.mark.parametrize("threads", [256, 512, 1024])
+@pytest.mark.parametrize("off", [-1, 0, 1])
+def test_narrow_queues(threads, off):
+    """Queues at the length up to which groups of four lanes expand them."""
+    g = narrow_layers(threads // 4 + off, seed=threads + off)
+    assert np.diff(g.row_ptr).max() <= 8
+    srcs = np.concatenate([np.zeros(3, np.int64), np.arange(0, g.n, max(1, g.n // 40))])
+    want = oracle.oracle_bc(g, srcs)
+    G = bc.Graph(g)
+    for opts in (dict(), dict(delta=1), dict(delta=1, far_buckets=1), dict(accumulate=2)):
+        got, _ = G.bc(srcs, wg_threads=threads, **opts)
+        assert np.all(got[want == 0] == 0)
+        nz = want != 0
+        assert np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11, opts
+    G.close()
