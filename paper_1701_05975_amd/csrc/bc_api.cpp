@@ -662,14 +662,23 @@ int64_t batch_cap(bc_graph *g)
 // Workgroups per source of the team form (team.hip); 1: one workgroup per
 // source.  A team gives up the distances in LDS and pays a barrier of 2 to 8 us
 // per step, so it needs enough arcs per source and enough members.  Measured, ms
-// with one workgroup / with the team (members): Barabasi-Albert 1M, 10M arcs: 1
-// source 51.7 / 7.0 (32), 16 sources 72 / 15.8 (16), 64 sources 98.7 / 51.8 (4);
-// R-MAT scale 20: 1 source 40.6 / 11.5 (32), 48 sources 62 / 41.7 (5), 64 sources
-// 67.8 / 52 (4), 128 sources 81 / 101 (2: not used); Barabasi-Albert 100k, 1M
-// arcs: 1 source 4.2 / 1.6 (32), 16 sources 4.4 / 2.6 (8), 64 sources 5.3 / 5.8
-// (4: not used); ER 40k, 320k arcs: 1 source 1.17 / 0.86 (16), 16 sources 1.32 /
-// 1.30 (4: not used).  Graphs of at most 8 arcs a vertex (grids) have frontiers
-// that one workgroup handles: 300 x 300 grid, 1 source 7.3 / 14.2 (4).
+// with one workgroup / with the team (members):
+//   Barabasi-Albert 1M, 10M arcs: 1 source 51.7 / 5.0 (32), 16 sources 72 / 13.2
+//   (16), 64 65.9 / 38.0 (4), 80 70.5 / 46.6 (3), 128 82.4 / 73.3 (2);
+//   ER 500k, 4M arcs: 16 22.8 / 6.4 (16), 85 33.4 / 28.3 (3), 128 39.0 / 35.3 (2);
+//   R-MAT scale 20, 16M arcs, where a few hubs take so many arcs that the
+//   distances in LDS answer most checks: 64 37.4 / 34.3 (4), 80 39.4 / 42.9 (3), 128
+//   46.2 / 64.4 (2).
+// Below 4M, a team of every second CU is better than one of all where it has 8
+// members (fewer workgroups wait in barriers), else all CUs are:
+//   R-MAT scale 17, 1.9M arcs: 8 sources 4.0 / 2.4 (16), 2.9 (32), 32 4.3 / 4.1 (8),
+//   48 4.4 / 5.3 (5); Kronecker scale 17: 16 6.3 / 3.1 (8), 3.3 (16), 32 6.9 / 4.5
+//   (8); Kronecker scale 16: 32 3.3 / 2.6 (8); Barabasi-Albert 100k, 1M arcs: 8
+//   3.2 / 1.9 (16), 16 3.2 / 2.3 (8), 24 3.25 / 3.07 (10), 32 3.27 / 3.38 (8);
+//   ER 40k, 320k arcs: 1 source 1.17 / 0.86 (16), 8 1.18 / 1.14 (16), 16 1.24 / 1.70
+//   (16, every CU).
+// Graphs of at most 8 arcs a vertex (grids) have frontiers that one workgroup
+// handles: 300 x 300 grid, 1 source 7.3 / 14.2 (4).
 static int team_size(const bc_graph *g, const bc_options &o, int64_t k)
 {
     const bool open = o.wg_threads == 0 && o.lds_vertices == 0 && o.lds_bits == 0 &&
@@ -679,11 +688,13 @@ static int team_size(const bc_graph *g, const bc_options &o, int64_t k)
     const int64_t work = g->nnz + g->n;
     if (!open || k < 1 || g->maxdeg <= 8 || work < 300000)
         return 1;
-    // the smaller graphs keep half of the GPU free of barriers
-    const int64_t large = work >= 4000000;
-    const int64_t w = std::min<int64_t>(g->num_cus / (large ? 1 : 2) / k, work < 1000000 ? 16 : 32);
-    const int64_t least = large ? 4 : work < 1000000 ? 16 : 8;
-    return w >= least ? (int)w : 1;
+    const int64_t all = std::min<int64_t>(g->num_cus / k, work < 1000000 ? 16 : 32);
+    if (work >= 4000000)
+        return all >= (g->maxdeg > g->n / 50 ? 4 : 2) ? (int)all : 1;
+    const int64_t half = std::min<int64_t>(g->num_cus / 2 / k, work < 1000000 ? 16 : 32);
+    if (half >= (work < 1000000 ? 16 : 8))
+        return (int)half;
+    return work >= 1000000 && all >= (work >= 1500000 ? 8 : 10) ? (int)all : 1;
 }
 
 ResolvedOptions resolve_options(bc_graph *g, const bc_options *opt, int64_t k, bool teams)

@@ -97,6 +97,22 @@ def test_team_distance_bounds(n, m, whi):
     G.close()
 
 
+@pytest.mark.parametrize("n, m, k", [(200_000, 2_000_000, 80), (200_000, 2_000_000, 128),
+                                     (80_000, 800_000, 32), (60_000, 600_000, 25)])
+def test_small_teams(n, m, k):
+    """Teams of two and three on the largest graphs, of every compute unit on the
+    middle ones."""
+    g = gg.er_graph(n, m, 1, 100, seed=68)
+    G = bc.Graph(g)
+    four = gg.sample_sources(g, 4, seed=4)
+    s = np.resize(four, k)
+    want = sum(np.count_nonzero(s == v) * oracle.oracle_bc(g, np.array([v])) for v in four)
+    got, st = G.bc(s)
+    assert st["lds_vertices"] == 0, st
+    close(got, want, 1e-11)
+    G.close()
+
+
 def test_team_edges_and_errors():
     torch = pytest.importorskip("torch")
     g = gg.er_graph(40_000, 160_000, 1, 5, seed=65)
