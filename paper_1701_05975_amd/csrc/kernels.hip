@@ -1177,7 +1177,7 @@ __global__ void k_fill_u64(unsigned long long *p, size_t count, unsigned long lo
         p[i] = value;
 }
 
-// Clears the persistent parts of every slab (queue tags, far flags, header).
+// Clears the persistent parts of every slab (queue tags, flags, header).
 __global__ void k_slab_reset(char *slab_base, SlabLayout L, int nslabs, int n)
 {
     const int slot = blockIdx.y;
