@@ -1291,6 +1291,7 @@ static void launch_batched_t(const BatchArgs &a, int nslabs, hipStream_t st)
 // output, LDS distance width, far-bucket ring).  The ring and the 8-bit
 // distances are built for packed-arc graphs only; the others keep the
 // two-tier far pile and 16- or 32-bit distances.
+#ifndef BC_FOR_EACH_BATCHED
 #define BC_FOR_EACH_BATCHED(X)                                                                  \
     X(true, 256, false, 32, false) X(true, 256, true, 32, false)                               \
     X(true, 512, false, 32, false) X(true, 512, true, 32, false)                               \
@@ -1316,6 +1317,7 @@ static void launch_batched_t(const BatchArgs &a, int nslabs, hipStream_t st)
     X(true, 1024, false, 32, true) X(true, 1024, true, 32, true)                               \
     X(true, 1024, false, 16, true) X(true, 1024, true, 16, true)                               \
     X(true, 1024, false, 8, true) X(true, 1024, true, 8, true)
+#endif
 
 hipError_t launch_batched(const BatchArgs &a, bool packed, int nt, bool atomic_bc, int nslabs,
                           hipStream_t st)

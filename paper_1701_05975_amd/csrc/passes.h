@@ -342,14 +342,16 @@ __device__ __forceinline__ void relax_commit(const Slab &S, const ExpandCtx &c, 
         int base = 0;
         if (lane < 4 && add > 0)
             base = atomicAdd(at, add);
+        const int b0 = __builtin_amdgcn_readlane(base, 0), b1 = __builtin_amdgcn_readlane(base, 1),
+                  b2 = __builtin_amdgcn_readlane(base, 2), b3 = __builtin_amdgcn_readlane(base, 3);
         if (pn)
-            c.next_q[__builtin_amdgcn_readlane(base, 0) + (int)lanes_below(mn)] = (int32_t)u;
+            c.next_q[b0 + (int)lanes_below(mn)] = (int32_t)u;
         if (pm)
-            c.order[__builtin_amdgcn_readlane(base, 1) + (int)lanes_below(mm)] = (int32_t)u;
+            c.order[b1 + (int)lanes_below(mm)] = (int32_t)u;
         if (pf)
-            c.far_q[__builtin_amdgcn_readlane(base, 2) + (int)lanes_below(mf)] = (int32_t)u;
+            c.far_q[b2 + (int)lanes_below(mf)] = (int32_t)u;
         if (po)
-            c.outer_q[__builtin_amdgcn_readlane(base, 3) + (int)lanes_below(mo)] = (int32_t)u;
+            c.outer_q[b3 + (int)lanes_below(mo)] = (int32_t)u;
     }
 }
 
@@ -540,7 +542,9 @@ __device__ __forceinline__ void expand_pass(const DevGraph &g, const Slab &S, co
             if (valid) {
                 beg = g.row[v];
                 end = g.row[v + 1];
-                if (v < S.HQ)
+                // once per queue entry: the pass that listed a hub cleared its
+                // bit, and by now the bit can stand for an entry of next_q
+                if (!hubs && v < S.HQ)
                     qbit_clear(S, (uint32_t)v);
                 dv = dist_get(S, v);
             }

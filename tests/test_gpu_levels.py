@@ -99,3 +99,30 @@ def test_narrow_queues(threads, off):
         nz = want != 0
         assert np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11, opts
     G.close()
+
+
+@pytest.mark.parametrize("n, hub", [(300, 64), (640, 0), (1024, 0)])
+@pytest.mark.parametrize("threads", [256, 1024])
+def test_hubs_that_improve_each_other(n, hub, threads):
+    """Complete graphs, every vertex a hub: their distances fall while their own
+    lists are expanded, in one wide band or in many."""
+    rng = np.random.default_rng(n)
+    a, b = np.triu_indices(n, 1)
+    w = rng.integers(1, 1001, a.shape[0])
+    g = gg.csr_from_arcs(n, np.concatenate([a, b]), np.concatenate([b, a]),
+                         np.concatenate([w, w]), directed=False, m=a.shape[0])
+    srcs = np.array([0, n // 2, n - 1, 0], np.int32)
+    want = oracle.oracle_bc(g, srcs)
+    od, osg, _, _ = oracle.oracle_source_state(g, 1)
+    G = bc.Graph(g)
+    for opts in (dict(), dict(delta=1 << 20), dict(delta=3, far_buckets=1),
+                 dict(far_buckets=2, lds_bits=16), dict(delta=1 << 20, lds_bits=16)):
+        got, st = G.bc(srcs, wg_threads=threads, wg_min_deg=hub, **opts)
+        assert st["lds_vertices"] > 0
+        assert np.all(got[want == 0] == 0)
+        nz = want != 0
+        # sums of at most a few thousand non-negative terms: 1e-16 relative each
+        assert np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11, opts
+        d, sg, _ = G.source_state(1, wg_threads=threads, wg_min_deg=hub, **opts)
+        assert np.array_equal(d, od) and np.array_equal(sg, osg), opts
+    G.close()

@@ -1,0 +1,43 @@
+"""The batched kernels' own code on the CPU (tests/lanes): a workgroup is a host
+thread, its work-items are fibers that meet at cross-lane operations and barriers,
+and waves take turns at random.  The state slab has guard words behind every array,
+which a write out of range changes, and a barrier that not every lane reaches ends
+the run; the centralities are compared with a plain Brandes."""
+from __future__ import annotations
+
+import os
+import subprocess
+
+import pytest
+
+from paper_1701_05975_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LANES = os.path.join(HERE, "lanes")
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    exe = tmp_path_factory.mktemp("lanes") / "kernels_check"
+    cmd = ["g++", "-std=c++17", "-O1", "-w", "-pthread", "-fno-extern-tls-init",
+           "-U_FORTIFY_SOURCE", f"-I{LANES}", f"-I{build.CSRC}",
+           os.path.join(LANES, "kernels_check.cpp"), "-o", str(exe)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+
+    def run(*args):
+        r = subprocess.run([str(exe), *map(str, args)], capture_output=True, text=True,
+                           timeout=300)
+        assert r.stdout.strip().endswith("OK"), (args, r.stdout[-500:], r.stderr[-500:])
+
+    return run
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+@pytest.mark.parametrize("n, degree, wmax, delta, wg_deg", [
+    (200, 190, 1000, 2000, 64), (300, 298, 255, 1000, 64), (300, 298, 255, 100, 64),
+    (640, 1100, 1000, 2000, 512)])
+def test_hubs_that_improve_each_other(check, n, degree, wmax, delta, wg_deg, seed):
+    """Dense graphs, most of whose vertices are hubs: a queue holds each vertex at
+    most once, whatever the band width."""
+    check("batched", n, degree, wmax, delta, wg_deg, seed)
