@@ -606,8 +606,11 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             if constexpr (LB == 8) {
                 // every vertex below the closed band's threshold is settled and
                 // every later offered value lies above it
-                if (C.thr - S.base8 > LDS8_REBASE) {
-                    const uint32_t nb = C.thr;
+                // (the threshold that every thread holds: thread 0 may be setting the
+                // next one already, and a wave that saw it would be alone in the
+                // barrier below)
+                if (ec.thr - S.base8 > LDS8_REBASE) {
+                    const uint32_t nb = ec.thr;
                     lds8_rebase(S, nb, tid, NT);
                     __syncthreads();
                     S.base8 = nb;

@@ -11,7 +11,7 @@
 thread_local uint32_t lds_dist[40 * 1024], seen_bounds[40 * 1024];
 
 #define BC_FOR_EACH_BATCHED(X) \
-    X(true, 256, true, 32, false) X(true, 256, true, 16, true)
+    X(true, 256, true, 32, false) X(true, 256, true, 16, true) X(true, 256, true, 8, false)
 #include "kernels.hip"
 #include "team.hip"
 
@@ -215,7 +215,7 @@ int batched(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed)
 {
     const Graph g = make_graph(n, degree, wmax, seed);
     Run r(g, {0, n / 2, n - 1}, 1, delta);
-    for (int lb : {32, 16}) {
+    for (int lb : {32, 16, 8}) {
         r.reset();
         r.a.H = n - n / 16;
         r.a.lds_bits = lb;

@@ -116,7 +116,8 @@ def test_hubs_that_improve_each_other(n, hub, threads):
     od, osg, _, _ = oracle.oracle_source_state(g, 1)
     G = bc.Graph(g)
     for opts in (dict(), dict(delta=1 << 20), dict(delta=3, far_buckets=1),
-                 dict(far_buckets=2, lds_bits=16), dict(delta=1 << 20, lds_bits=16)):
+                 dict(far_buckets=2, lds_bits=16), dict(delta=1 << 20, lds_bits=8),
+                 dict(delta=16, lds_bits=8, far_buckets=2)):
         got, st = G.bc(srcs, wg_threads=threads, wg_min_deg=hub, **opts)
         assert st["lds_vertices"] > 0
         assert np.all(got[want == 0] == 0)

@@ -41,3 +41,11 @@ def test_hubs_that_improve_each_other(check, n, degree, wmax, delta, wg_deg, see
     """Dense graphs, most of whose vertices are hubs: a queue holds each vertex at
     most once, whatever the band width."""
     check("batched", n, degree, wmax, delta, wg_deg, seed)
+
+
+@pytest.mark.parametrize("seed", [1, 2, 3])
+@pytest.mark.parametrize("delta", [3, 10, 70])
+def test_bands_of_a_sparse_graph(check, delta, seed):
+    """Many bands of few vertices, with each width of the resident distances: waves
+    that reach a band change late take the same way as the first one."""
+    check("batched", 120, 8, 20, delta, 512, seed)
