@@ -925,6 +925,7 @@ void launch_batched_pass(bc_graph *g, const ResolvedOptions &r, const int32_t *s
         t.bshift = 0;
         while (((int64_t)(SEEN_WIN - SEEN_REBASE) << t.bshift) < (int64_t)g->wmax + r.delta)
             ++t.bshift;
+        t.looks = TEAM_WAIT_LOOKS;
         hip_check(launch_team(t, g->packed, st), "team kernel");
     } else {
         hip_check(launch_batched(a, g->packed, r.wg_threads, atomic_bc, nslabs, st),

@@ -62,6 +62,7 @@ struct TeamArgs {
     int size;     // most workgroups of a team
     int bounds;   // vertices with a distance bound in LDS, a multiple of 16
     int bshift;   // and the unit of the bounds
+    unsigned int looks; // a member's looks at a barrier before it has failed
 };
 
 // Phase machine of the plain form (device memory, one per graph).
@@ -104,6 +105,8 @@ hipError_t launch_batched(const BatchArgs &a, bool packed, int nt, bool atomic_b
 #define TEAM_THREADS 1024
 // LDS of a team workgroup besides the bounds
 #define TEAM_LDS_CTL 1024
+// TeamArgs::looks: at 0.5 us or more each, no interval of work is as long
+#define TEAM_WAIT_LOOKS 0x80000000u
 hipError_t launch_team(const TeamArgs &a, bool packed, hipStream_t st);
 int batched_blocks_per_cu_lds(bool packed, int nt, bool atomic_bc, int lds_bits, size_t lds_bytes);
 int batched_blocks_per_cu(bool packed, int nt, bool atomic_bc, int lds_bits);

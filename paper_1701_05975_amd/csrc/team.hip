@@ -27,7 +27,6 @@
 
 #define TEAM_CLOSED 0x80000000u
 #define TEAM_JOIN_TICKS 2000ll          // 20 us of the 100 MHz device clock
-#define TEAM_WAIT_TICKS (100000000ll * 8) // a barrier that waits 8 s has failed
 
 extern __shared__ uint32_t seen_bounds[];
 
@@ -62,13 +61,17 @@ struct TeamSync {
     TeamCtl *ctl;
     unsigned int epoch; // arrivals that complete the next barrier (thread 0)
     int interval;       // barrier intervals so far, mod 3
+    unsigned int looks; // looks at a barrier before it has failed
 };
 
 // Barrier of the team.  The release before and the acquire after it (of thread
 // 0, between workgroup barriers) order every member's accesses; a barrier
 // costs 1.7 us for a team of 2 to 8 alone on the GPU, 8 us when 256 workgroups
-// are in barriers at once.  `par`, `band`: which of the source and far pile
-// words to read.
+// are in barriers at once.  All members run and none leaves early, so each wait
+// ends; the bound is there for the case that this is not so.  It counts looks,
+// not time: on a GPU shared with other processes a team is slow while it is off
+// the GPU, and then all of it is.  `par`, `band`: which of the source and far
+// pile words to read.
 __device__ __forceinline__ bool team_barrier(TeamWg &W, TeamSync &y, int par, int band)
 {
     // every wave's stores have reached the L2 before thread 0 releases them (a
@@ -84,18 +87,14 @@ __device__ __forceinline__ bool team_barrier(TeamWg &W, TeamSync &y, int par, in
         y.epoch += (unsigned int)W.members;
         __threadfence();
         __hip_atomic_fetch_add(&c->arrived, 1u, __ATOMIC_RELAXED, AG_SCOPE);
-        long long t0 = 0;
-        for (int spins = 0; (int)(ag_load(&c->arrived) - y.epoch) < 0; ++spins) {
+        for (unsigned int looks = 0; (int)(ag_load(&c->arrived) - y.epoch) < 0;) {
             __builtin_amdgcn_s_sleep(1);
-            if ((spins & 1023) == 1023) {
-                const long long t = wall_clock64();
-                t0 = t0 ? t0 : t;
-                if (t - t0 > TEAM_WAIT_TICKS)
-                    ag_store(&c->failed, 1u);
-                if (ag_load(&c->failed)) {
-                    W.failed = 1;
-                    break;
-                }
+            const bool late = ++looks >= y.looks;
+            if (late)
+                ag_store(&c->failed, 1u);
+            if ((late || (looks & 1023u) == 0u) && ag_load(&c->failed)) {
+                W.failed = 1;
+                break;
             }
         }
         __threadfence();
@@ -118,7 +117,7 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
     const int tid = threadIdx.x;
     const DevGraph &g = a.g;
     const int n = g.n;
-    TeamSync y{nullptr, 0u, 0};
+    TeamSync y{nullptr, 0u, 0, ta.looks};
     if (tid == 0) {
         W.failed = 0;
         W.team = -1;

@@ -79,6 +79,11 @@ inline unsigned &seed()
     static unsigned s = 1;
     return s;
 }
+inline std::function<long long()> &clock_step()
+{
+    static std::function<long long()> f = [] { return 1ll; };
+    return f;
+}
 inline thread_local Group *group = nullptr;
 inline thread_local dim3 lane_index;
 
@@ -319,11 +324,11 @@ template <class T> T __shfl_xor(T x, int mask)
 }
 inline int __popcll(uint64_t x) { return __builtin_popcountll(x); }
 inline int __ffsll(unsigned long long x) { return __builtin_ffsll((long long)x); }
-// ticks of a clock that only goes on when it is read
+// ticks of a clock that only goes on when it is read, in steps of lanes::clock_step()
 inline long long wall_clock64()
 {
     static std::atomic<long long> t{0};
-    return ++t;
+    return t += lanes::clock_step()();
 }
 
 inline int __builtin_amdgcn_readlane(int x, int from)

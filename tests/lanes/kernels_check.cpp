@@ -1,6 +1,7 @@
 // The batched kernels, run on the CPU (hip/hip_runtime.h beside this file) with
 // guard words behind every array of a state slab.  Prints OK, or what is wrong.
 //   kernels_check batched n degree wmax delta wg_deg seed
+//   kernels_check team n degree wmax delta wg_deg seed teams members clock_step
 #include <algorithm>
 #include <cmath>
 #include <queue>
@@ -234,19 +235,56 @@ int batched(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed)
     return 0;
 }
 
+// clock_step: ticks of the device clock between two reads of it, once the teams
+// have formed.
+int team(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed, int teams, int members,
+         int clock_step)
+{
+    const Graph g = make_graph(n, degree, wmax, seed);
+    Run r(g, {0, n / 2, n - 1}, teams, delta);
+    r.a.H = 0;
+    r.a.lds_bits = 32;
+    r.a.wg_deg = (uint32_t)wg_deg;
+    r.a.hubs = g.maxdeg > wg_deg;
+    r.a.narrow = 0;
+    std::vector<TeamCtl> ctl(teams);
+    TeamArgs t;
+    t.b = r.a;
+    t.ctl = ctl.data();
+    t.teams = teams;
+    t.size = members;
+    t.bounds = (n / 2 + 15) / 16 * 16;
+    t.bshift = 0;
+    while (((SEEN_WIN - SEEN_REBASE) << t.bshift) < (uint32_t)(wmax + delta))
+        ++t.bshift;
+    t.looks = TEAM_WAIT_LOOKS;
+    lanes::clock_step() = [&]() -> long long {
+        for (auto &c : ctl)
+            if (lanes::load(&c.members) == 0)
+                return 1;
+        return clock_step;
+    };
+    if (launch_team(t, true, nullptr) != hipSuccess)
+        return printf("launch\n"), 1;
+    const std::string bad = r.check(g);
+    return bad.empty() ? 0 : (printf("%s\n", bad.c_str()), 1);
+}
+
 } // namespace
 
 int main(int argc, char **argv)
 {
-    if (argc != 8)
+    int v[9] = {};
+    if (argc != 8 && argc != 11)
         return 2;
-    int v[6];
-    for (int i = 0; i < 6; ++i)
-        v[i] = atoi(argv[2 + i]);
+    for (int i = 2; i < argc; ++i)
+        v[i - 2] = atoi(argv[i]);
     lanes::seed() = (unsigned)v[5];
     int r = 2;
     if (!strcmp(argv[1], "batched"))
         r = batched(v[0], v[1], v[2], v[3], v[4], (unsigned)v[5]);
+    else if (!strcmp(argv[1], "team"))
+        r = team(v[0], v[1], v[2], v[3], v[4], (unsigned)v[5], v[6], v[7], v[8]);
     if (r == 0)
         printf("OK\n");
     return r;

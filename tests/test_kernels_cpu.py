@@ -49,3 +49,13 @@ def test_bands_of_a_sparse_graph(check, delta, seed):
     """Many bands of few vertices, with each width of the resident distances: waves
     that reach a band change late take the same way as the first one."""
     check("batched", 120, 8, 20, delta, 512, seed)
+
+
+@pytest.mark.parametrize("seed", [1, 2, 3])
+@pytest.mark.parametrize("n, degree, wmax, delta, wg_deg, teams, members", [
+    (200, 12, 30, 15, 16, 2, 2), (120, 110, 255, 100, 64, 1, 3), (150, 4, 1000, 300, 512, 3, 1)])
+def test_teams(check, n, degree, wmax, delta, wg_deg, teams, members, seed):
+    """Teams in step and with hubs, and one whose members wait for long by the clock (off
+    the GPU for ten seconds between two reads of it)."""
+    for step in (1, 10**9):
+        check("team", n, degree, wmax, delta, wg_deg, seed, teams, members, step)
