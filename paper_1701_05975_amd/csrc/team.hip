@@ -62,6 +62,7 @@ struct TeamSync {
     unsigned int epoch; // arrivals that complete the next barrier (thread 0)
     int interval;       // barrier intervals so far, mod 3
     unsigned int looks; // looks at a barrier before it has failed
+    unsigned long long *err;
 };
 
 // Barrier of the team.  The release before and the acquire after it (of thread
@@ -70,8 +71,10 @@ struct TeamSync {
 // are in barriers at once.  All members run and none leaves early, so each wait
 // ends; the bound is there for the case that this is not so.  It counts looks,
 // not time: on a GPU shared with other processes a team is slow while it is off
-// the GPU, and then all of it is.  `par`, `band`: which of the source and far
-// pile words to read.
+// the GPU, and then all of it is.  A member that sees a failure, its own or
+// another's, says so itself: the first member may be the one that came late and
+// sees its barriers complete, and its next one can be that of a new source.
+// `par`, `band`: which of the source and far pile words to read.
 __device__ __forceinline__ bool team_barrier(TeamWg &W, TeamSync &y, int par, int band)
 {
     // every wave's stores have reached the L2 before thread 0 releases them (a
@@ -92,10 +95,8 @@ __device__ __forceinline__ bool team_barrier(TeamWg &W, TeamSync &y, int par, in
             const bool late = ++looks >= y.looks;
             if (late)
                 ag_store(&c->failed, 1u);
-            if ((late || (looks & 1023u) == 0u) && ag_load(&c->failed)) {
-                W.failed = 1;
+            if (late || ((looks & 1023u) == 0u && ag_load(&c->failed)))
                 break;
-            }
         }
         __threadfence();
         for (int i = 0; i < TEAM_STEP_WORDS; ++i)
@@ -103,6 +104,10 @@ __device__ __forceinline__ bool team_barrier(TeamWg &W, TeamSync &y, int par, in
         W.far_cnt = ag_load(&c->far_cnt[band]);
         W.far_min = ag_load(&c->far_min[band]);
         W.src = ag_load(&c->src[par]);
+        if (ag_load(&c->failed)) {
+            W.failed = 1;
+            atomicOr(y.err, (unsigned long long)BC_ERRBIT_INTERNAL);
+        }
     }
     y.interval = y.interval == 2 ? 0 : y.interval + 1;
     __syncthreads();
@@ -117,7 +122,7 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
     const int tid = threadIdx.x;
     const DevGraph &g = a.g;
     const int n = g.n;
-    TeamSync y{nullptr, 0u, 0, ta.looks};
+    TeamSync y{nullptr, 0u, 0, ta.looks, a.err};
     if (tid == 0) {
         W.failed = 0;
         W.team = -1;
@@ -463,8 +468,9 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
     flush(st_dag, &a.stats->dag);
     flush(st_imp, &a.stats->improvements);
     if (lead) {
-        S.hdr[0] = gen;
-        S.hdr[1] = lvl;
+        // (after a failed barrier another member can be a round further on)
+        S.hdr[0] = gen + W.failed;
+        S.hdr[1] = lvl + W.failed;
         atomicAdd(&a.stats->sigma_rounds, srounds);
         atomicAdd(&a.stats->delta_rounds, drounds);
         for (int i = 0; i < 5; ++i)

@@ -1,7 +1,7 @@
 // The batched kernels, run on the CPU (hip/hip_runtime.h beside this file) with
 // guard words behind every array of a state slab.  Prints OK, or what is wrong.
 //   kernels_check batched n degree wmax delta wg_deg seed
-//   kernels_check team n degree wmax delta wg_deg seed teams members clock_step
+//   kernels_check team n degree wmax delta wg_deg seed teams members clock_step looks
 #include <algorithm>
 #include <cmath>
 #include <queue>
@@ -236,9 +236,10 @@ int batched(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed)
 }
 
 // clock_step: ticks of the device clock between two reads of it, once the teams
-// have formed.
+// have formed.  looks: at a barrier, before a member takes it for failed (0: the
+// library's own); a team whose barrier failed has to say so.
 int team(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed, int teams, int members,
-         int clock_step)
+         int clock_step, int looks)
 {
     const Graph g = make_graph(n, degree, wmax, seed);
     Run r(g, {0, n / 2, n - 1}, teams, delta);
@@ -257,7 +258,7 @@ int team(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed, int 
     t.bshift = 0;
     while (((SEEN_WIN - SEEN_REBASE) << t.bshift) < (uint32_t)(wmax + delta))
         ++t.bshift;
-    t.looks = TEAM_WAIT_LOOKS;
+    t.looks = looks > 0 ? (unsigned)looks : TEAM_WAIT_LOOKS;
     lanes::clock_step() = [&]() -> long long {
         for (auto &c : ctl)
             if (lanes::load(&c.members) == 0)
@@ -266,6 +267,13 @@ int team(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed, int 
     };
     if (launch_team(t, true, nullptr) != hipSuccess)
         return printf("launch\n"), 1;
+    for (auto &c : ctl)
+        if (looks > 0 && c.failed) {
+            if (r.err[0] != BC_ERRBIT_INTERNAL)
+                return printf("a barrier failed without an error\n"), 1;
+            printf("a barrier failed, ");
+            return 0;
+        }
     const std::string bad = r.check(g);
     return bad.empty() ? 0 : (printf("%s\n", bad.c_str()), 1);
 }
@@ -274,8 +282,8 @@ int team(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed, int 
 
 int main(int argc, char **argv)
 {
-    int v[9] = {};
-    if (argc != 8 && argc != 11)
+    int v[10] = {};
+    if (argc != 8 && argc != 12)
         return 2;
     for (int i = 2; i < argc; ++i)
         v[i - 2] = atoi(argv[i]);
@@ -284,7 +292,7 @@ int main(int argc, char **argv)
     if (!strcmp(argv[1], "batched"))
         r = batched(v[0], v[1], v[2], v[3], v[4], (unsigned)v[5]);
     else if (!strcmp(argv[1], "team"))
-        r = team(v[0], v[1], v[2], v[3], v[4], (unsigned)v[5], v[6], v[7], v[8]);
+        r = team(v[0], v[1], v[2], v[3], v[4], (unsigned)v[5], v[6], v[7], v[8], v[9]);
     if (r == 0)
         printf("OK\n");
     return r;

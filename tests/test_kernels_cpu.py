@@ -29,6 +29,7 @@ def check(tmp_path_factory):
         r = subprocess.run([str(exe), *map(str, args)], capture_output=True, text=True,
                            timeout=300)
         assert r.stdout.strip().endswith("OK"), (args, r.stdout[-500:], r.stderr[-500:])
+        return r.stdout
 
     return run
 
@@ -58,4 +59,13 @@ def test_teams(check, n, degree, wmax, delta, wg_deg, teams, members, seed):
     """Teams in step and with hubs, and one whose members wait for long by the clock (off
     the GPU for ten seconds between two reads of it)."""
     for step in (1, 10**9):
-        check("team", n, degree, wmax, delta, wg_deg, seed, teams, members, step)
+        check("team", n, degree, wmax, delta, wg_deg, seed, teams, members, step, 0)
+
+
+@pytest.mark.parametrize("looks", [1, 3, 10, 30, 100, 300, 1000, 3000])
+def test_failed_team_barrier_is_reported(check, looks):
+    """Members that give a barrier up after a few looks, each at another one: every
+    workgroup ends, and a result that lacks a share is never taken for one."""
+    failed = sum("failed" in check("team", 200, 12, 30, 15, 16, seed, 2, 2, 1, looks)
+                 for seed in range(1, 9))
+    assert failed > 0 or looks > 100
