@@ -820,8 +820,15 @@ void create_graph_device(int32_t n, int64_t nnz64, const int64_t *row_ptr, const
                                (uint32_t *)tmp.keys.p, (uint32_t *)tmp.vals.p);
             const uint32_t *sorted = radix_sort<uint32_t>(tmp, nnz, colbits, st);
             DevBuf &from = sorted == tmp.vals.p ? tmp.vals : tmp.v2;
-            std::swap(g->tarc.p, from.p);
-            std::swap(g->tarc.bytes, from.bytes);
+            if (from.bytes == (size_t)nnz * 4) {
+                std::swap(g->tarc.p, from.p);
+                std::swap(g->tarc.bytes, from.bytes);
+            } else { // sized for the renumbering's n keys
+                g->tarc.alloc((size_t)nnz * 4);
+                hip_check(hipMemcpyAsync(g->tarc.p, from.p, (size_t)nnz * 4,
+                                         hipMemcpyDeviceToDevice, st),
+                          "copy");
+            }
         } else if (nnz > 0) {
             const uint32_t *vals =
                 sort_arcs(nnz, head, nullptr, 0, colbits, nullptr, 0, nullptr, tmp, st);

@@ -202,3 +202,24 @@ def test_reverse_arcs_of_rows_in_any_order(in_order, hub):
         ds = _status(lambda: bc.bc_create_graph_device(
             b.n, int(col_t.numel()), rp_t.data_ptr(), col_t.data_ptr(), w_t.data_ptr(), 0))
         assert hs == ds == bc.BC_E_GRAPH, what
+
+
+@pytest.mark.parametrize("n, m", [(5000, 600), (600, 5000), (4096, 4096), (3, 1)])
+def test_directed_without_edges(n, m):
+    """The transpose sorted as packed arcs, of more and of fewer arcs than vertices: the
+    same graph, in the same memory, as from host arrays."""
+    rng = np.random.default_rng(n + m)
+    head = np.where(rng.random(m) < 0.5, 1, rng.integers(0, n, m))  # renumbered: one big hub
+    g = gg.csr_from_arcs(n, rng.integers(0, n, m), head, rng.integers(1, 9, m), directed=True)
+    for keep in (False, True):
+        H = bc.Graph(g, keep_order=keep)
+        D = device_graph(g, keep_order=keep)
+        assert D.info() == H.info()
+        for s in {0, 1, n - 1, int(np.argmax(np.diff(g.row_ptr)))}:
+            dh, sh, lh = H.source_state(s)
+            dd, sd, ld = D.source_state(s)
+            assert np.array_equal(dh, dd) and np.array_equal(sh, sd), s
+            rel_close(ld, lh, 1e-12)
+        rel_close(D.bc(None)[0], oracle.oracle_bc(g, np.arange(n)), 1e-9)
+        H.close()
+        D.close()
