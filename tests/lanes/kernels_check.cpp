@@ -1,6 +1,6 @@
 // The batched kernels, run on the CPU (hip/hip_runtime.h beside this file) with
 // guard words behind every array of a state slab.  Prints OK, or what is wrong.
-//   kernels_check batched n degree wmax delta wg_deg seed
+//   kernels_check batched n degree wmax delta wg_deg seed group
 //   kernels_check team n degree wmax delta wg_deg seed teams members clock_step looks
 #include <algorithm>
 #include <cmath>
@@ -212,7 +212,9 @@ struct Run {
     }
 };
 
-int batched(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed)
+// group: lanes per vertex in the expansion (0: arcs laid out flat, -1: flat, but
+// short queues in small groups).
+int batched(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed, int group)
 {
     const Graph g = make_graph(n, degree, wmax, seed);
     Run r(g, {0, n / 2, n - 1}, 1, delta);
@@ -225,7 +227,8 @@ int batched(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed)
         r.a.bcap = 4 * n / r.a.nbk;
         r.a.wg_deg = (uint32_t)wg_deg;
         r.a.hubs = g.maxdeg > wg_deg;
-        r.a.narrow = 0;
+        r.a.narrow = group < 0;
+        r.a.vw = group < 0 ? 0 : group;
         if (launch_batched(r.a, true, 256, true, 1, nullptr) != hipSuccess)
             return printf("no such kernel\n"), 1;
         const std::string bad = r.check(g);
@@ -283,14 +286,14 @@ int team(int n, int degree, int wmax, int delta, int wg_deg, unsigned seed, int 
 int main(int argc, char **argv)
 {
     int v[10] = {};
-    if (argc != 8 && argc != 12)
+    if (argc != 9 && argc != 12)
         return 2;
     for (int i = 2; i < argc; ++i)
         v[i - 2] = atoi(argv[i]);
     lanes::seed() = (unsigned)v[5];
     int r = 2;
     if (!strcmp(argv[1], "batched"))
-        r = batched(v[0], v[1], v[2], v[3], v[4], (unsigned)v[5]);
+        r = batched(v[0], v[1], v[2], v[3], v[4], (unsigned)v[5], v[6]);
     else if (!strcmp(argv[1], "team"))
         r = team(v[0], v[1], v[2], v[3], v[4], (unsigned)v[5], v[6], v[7], v[8], v[9]);
     if (r == 0)

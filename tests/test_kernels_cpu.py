@@ -41,7 +41,7 @@ def check(tmp_path_factory):
 def test_hubs_that_improve_each_other(check, n, degree, wmax, delta, wg_deg, seed):
     """Dense graphs, most of whose vertices are hubs: a queue holds each vertex at
     most once, whatever the band width."""
-    check("batched", n, degree, wmax, delta, wg_deg, seed)
+    check("batched", n, degree, wmax, delta, wg_deg, seed, 0)
 
 
 @pytest.mark.parametrize("seed", [1, 2, 3])
@@ -49,7 +49,15 @@ def test_hubs_that_improve_each_other(check, n, degree, wmax, delta, wg_deg, see
 def test_bands_of_a_sparse_graph(check, delta, seed):
     """Many bands of few vertices, with each width of the resident distances: waves
     that reach a band change late take the same way as the first one."""
-    check("batched", 120, 8, 20, delta, 512, seed)
+    check("batched", 120, 8, 20, delta, 512, seed, 0)
+
+
+@pytest.mark.parametrize("seed", [1, 2, 3])
+@pytest.mark.parametrize("group", [-1, 1, 4, 16, 64])
+def test_groups_of_lanes(check, group, seed):
+    """A group of lanes per queued vertex, also for short queues only: its lanes expand
+    the vertex from one distance, and an improvement meanwhile queues it again."""
+    check("batched", 206, 4, 20, 5000, 512, seed, group)
 
 
 @pytest.mark.parametrize("seed", [1, 2, 3])
