@@ -195,7 +195,7 @@ struct HostLayout {
     int32_t wmax = 1, maxdeg = 0;
     int wbytes = 1;
     uint32_t wshift = 0, wmask = 0;
-    double avg_deg = 0.0, wmean = 1.0;
+    double avg_deg = 0.0, wmean = 1.0, deg_spread = 0.0;
     std::vector<uint32_t> row, arc, trow, tarc;
     std::vector<int32_t> wt, twt; // only when the arcs are not packed
     std::vector<int32_t> perm, iperm;
@@ -268,8 +268,14 @@ static void build_host_layout(int32_t n, int64_t nnz, const int64_t *row_ptr, co
     L.wmask = L.packed ? (wbits == 0 ? 0u : (uint32_t)((1ull << wbits) - 1)) : 0u;
     L.wbytes = wmax <= 255 ? 1 : (wmax <= 65535 ? 2 : 4);
     int64_t nz_rows = 0;
-    for (int32_t v = 0; v < n; ++v)
+    double deg_sum = 0.0, deg_squares = 0.0;
+    for (int32_t v = 0; v < n; ++v) {
         nz_rows += row_ptr[v + 1] > row_ptr[v];
+        const double dg = (double)std::min<int64_t>(row_ptr[v + 1] - row_ptr[v], DEG_CAP);
+        deg_sum += dg;
+        deg_squares += dg * dg;
+    }
+    L.deg_spread = spread_of((double)nz_rows, deg_sum, deg_squares);
     L.avg_deg = nz_rows ? (double)nnz / (double)nz_rows : 0.0;
     double wsum = 0;
     for (int64_t e = 0; e < nnz; ++e)
@@ -419,6 +425,7 @@ static void create_graph(int32_t n, int64_t nnz, const int64_t *row_ptr, const i
     g->wbytes = L.wbytes;
     g->avg_deg = L.avg_deg;
     g->wmean = L.wmean;
+    g->deg_spread = L.deg_spread;
     g->renumbered = L.renumbered;
     g->host_iperm = L.iperm;
     upload(g->perm, L.perm, "upload numbering");
@@ -546,6 +553,25 @@ static void ensure_sources(bc_graph *g, int64_t k)
 // ---------------------------------------------------------------------------
 // Options
 // ---------------------------------------------------------------------------
+double spread_of(double rows, double sum, double squares)
+{
+    const double mean = sum / std::max(rows, 1.0);
+    return mean > 0.0 ? squares / rows / mean - mean : 0.0;
+}
+
+// Graphs whose frontiers stay narrow and whose paths are long: at most 8 arcs a
+// vertex, or fewer than 5 in the mean and even degrees (DEG_CAP), so that some
+// wider vertices in a grid or a road network change nothing.  By the most arcs of a
+// vertex alone, one of 10 arcs did (ms, without / with this rule): 300 x 300 grid, 1
+// source 18.1 / 7.2, 512 sources 30.6 / 15.5; 700 x 700 grid without a fifth of its
+// edges, 16 sources 87.7 / 27.2; ten paths of 1000 vertices at a hub, 1 source 12.0 /
+// 6.4, 1024 sources 66.6 / 13.4.  Random graphs of 4 arcs a vertex (spread 0.93) stay
+// out: their frontiers fill a team (ER 200k, 1 source 1.6 ms with, 26 without one).
+static bool narrow_graph(const bc_graph *g)
+{
+    return g->maxdeg <= 8 || (g->avg_deg < 5.0 && g->deg_spread < 0.5);
+}
+
 // Band width of the near-far split when the caller leaves it open.  Narrow
 // bands improve fewer distances twice (an improvement costs scattered atomics
 // and an expansion), wide ones fill the lanes and need fewer steps, so the best
@@ -556,9 +582,8 @@ static void ensure_sources(bc_graph *g, int64_t k)
 // / 64; R-MAT scale 14 15-31 / 32, 17 4-7 / 12, 20 2-4 / 5.  Against 4 maximum
 // weights over the average degree at any size: R-MAT scale 20, 256 sources 110 ->
 // 66 ms, Barabasi-Albert 100k, 1024 sources 37.3 -> 28.4, ER 500k, 256 sources 74 ->
-// 62.  Graphs of at most 8 arcs a vertex (grids) have narrow frontiers and long
-// paths, and want whole weights: 32 x 32 grid 8 maximum weights, 100 x 100 2 to 4,
-// 1000 x 1000 0.7 to 1.  A team pays a barrier over several workgroups per step
+// 62.  Graphs of narrow frontiers and long paths (narrow_graph) want whole weights:
+// 32 x 32 grid 8 maximum weights, 100 x 100 2 to 4, 1000 x 1000 0.7 to 1.  A team pays a barrier over several workgroups per step
 // and wants wider bands (Barabasi-Albert 1M 100-200, R-MAT scale 20 7-15, ER 500k
 // 50).  The plain form, which launches every step, keeps the size-independent
 // width.
@@ -568,7 +593,7 @@ int default_delta(const bc_graph *g, int form, int team)
     double d;
     if (form == BC_MODE_PLAIN || g->nnz == 0) {
         d = 4.0 * wmax / avg;
-    } else if (g->maxdeg <= 8) {
+    } else if (narrow_graph(g)) {
         d = 4.0 * wmax / avg * std::pow(1e6 / (double)g->n, 0.3);
     } else {
         d = (g->renumbered ? 0.2 : 0.5) * wmax *
@@ -590,15 +615,20 @@ int default_delta(const bc_graph *g, int form, int team)
 // 100k, 16 sources 15.3 / 8.8 / 5.5, 1024 sources 64 / 54 / 46.
 // Two exceptions: small graphs, whose frontiers do not fill 1024 threads (ER
 // 1000, 16 sources 0.25 / 0.22 / 0.22, all sources 0.49 / 0.56 / 0.80), and
-// graphs of at most 8 arcs a vertex, grids above all, whose frontiers stay
-// narrow at any size: more sources than CUs then run side by side (100 x 100
-// grid, 1024 sources 3.3 / 4.5 / 7.9; 300 x 300 grid, 512 sources 17.5 / 15.6 /
-// 21.3).
+// graphs whose frontiers stay narrow at any size, grids and rings above all: more
+// sources than CUs then run side by side (100 x 100 grid, 1024 sources 3.3 / 4.5 /
+// 7.9, with one vertex of 10 arcs 3.4 / 5.3 / 9.1; 300 x 300 grid, 512 sources 17.5 /
+// 15.6 / 21.3; ring of 20,000 vertices of 10 arcs, 512 sources 29.8 / 28.6 / 49.3,
+// 1024 34.6 / 57 / 98).  Even degrees tell them (a ring with shortcuts counts as one,
+// 100,000 vertices of 10 arcs, 512 sources 17.7 / 14.4 / 14.3) up to 32 arcs a
+// vertex; denser graphs fill their frontiers (complete, 2500 vertices, 600 sources
+// 24.3 / 23.8 / 22.4).
 int default_wg_threads(const bc_graph *g, int64_t k)
 {
     if (g->n <= 2048)
         return k <= g->num_cus / 4 ? 512 : 256;
-    if (k <= g->num_cus || g->maxdeg > 8)
+    const bool even = g->deg_spread < 0.5 && g->avg_deg <= 32.0;
+    if (k <= g->num_cus || (g->maxdeg > 8 && !even))
         return 1024;
     return k <= 2 * (int64_t)g->num_cus ? 512 : 256;
 }
@@ -677,8 +707,8 @@ int64_t batch_cap(bc_graph *g)
 //   3.2 / 1.9 (16), 16 3.2 / 2.3 (8), 24 3.25 / 3.07 (10), 32 3.27 / 3.38 (8);
 //   ER 40k, 320k arcs: 1 source 1.17 / 0.86 (16), 8 1.18 / 1.14 (16), 16 1.24 / 1.70
 //   (16, every CU).
-// Graphs of at most 8 arcs a vertex (grids) have frontiers that one workgroup
-// handles: 300 x 300 grid, 1 source 7.3 / 14.2 (4).
+// Narrow graphs (grids) have frontiers that one workgroup handles: 300 x 300 grid,
+// 1 source 7.3 / 14.2 (4).
 static int team_size(const bc_graph *g, const bc_options &o, int64_t k)
 {
     const bool open = o.wg_threads == 0 && o.lds_vertices == 0 && o.lds_bits == 0 &&
@@ -686,7 +716,7 @@ static int team_size(const bc_graph *g, const bc_options &o, int64_t k)
                       o.dep_mode != 2 && o.accumulate == 0 && !o.autotune &&
                       (o.batch == 0 || o.batch >= k);
     const int64_t work = g->nnz + g->n;
-    if (!open || k < 1 || g->maxdeg <= 8 || work < 300000)
+    if (!open || k < 1 || narrow_graph(g) || work < 300000)
         return 1;
     const int64_t all = std::min<int64_t>(g->num_cus / k, work < 1000000 ? 16 : 32);
     if (work >= 4000000)

@@ -108,7 +108,8 @@ struct bc_graph {
     int32_t maxdeg = 0;
     int32_t n_act = 0; // vertices from here on have no in-arcs (see DevGraph)
     int wbytes = 1;
-    double avg_deg = 0.0, wmean = 1.0;
+    double avg_deg = 0.0, wmean = 1.0; // arcs per vertex that has any, mean weight
+    double deg_spread = 0.0; // variance over mean of the degrees (spread_of)
     bool packed = false;
     bool renumbered = false; // device ids are by decreasing in-degree
     uint32_t wshift = 0, wmask = 0;
@@ -160,6 +161,11 @@ struct bc_result {
 };
 
 SlabLayout slab_layout(int32_t n, int64_t pred_slots);
+// Variance over mean of `rows` degrees of at least 1, given the sums of the degrees
+// and of their squares, each degree taken as DEG_CAP if above: 1 where arcs are
+// drawn at random, near 0 in grids, meshes and roads, also with some hubs.
+#define DEG_CAP 64
+double spread_of(double rows, double sum, double squares);
 // Band width for an execution form with `team` workgroups per source.
 int default_delta(const bc_graph *g, int form, int team);
 // Threads per workgroup for k sources when the caller leaves them open.

@@ -262,6 +262,7 @@ struct IngestSummary {
     unsigned long long bad_col;  // smallest arc whose head is out of range
     unsigned long long bad_w;    // smallest arc whose weight is below 1
     unsigned long long wsum;     // sum of the weights
+    unsigned long long deg_sum, deg_squares; // of the degrees, at most DEG_CAP each
     unsigned int maxdeg, wmax, nz_rows, max_indeg;
     int32_t bad_w_value, bad_col_value;
     long long row0, rown;        // row_ptr[0], row_ptr[n]
@@ -354,18 +355,45 @@ __global__ void k_ingest_bad_values(const int32_t *col, const int32_t *w, Ingest
         sum->bad_w_value = w[sum->bad_w];
 }
 
-__global__ void k_max_indeg(const uint32_t *indeg, int32_t n, IngestSummary *sum)
+// The largest in-degree and the sums for the spread of the degrees; few workgroups,
+// which add once each (see k_ingest_check).
+__global__ __launch_bounds__(CHECK_NT) void k_degrees(const uint32_t *indeg, const int64_t *row_ptr,
+                                                      int32_t n, IngestSummary *sum)
 {
     uint32_t m = 0;
+    unsigned long long ds = 0, dq = 0;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < (size_t)n; i += stride)
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < (size_t)n; i += stride) {
         m = indeg[i] > m ? indeg[i] : m;
+        const long long d = row_ptr[i + 1] - row_ptr[i];
+        const unsigned long long x = d < 0 ? 0 : d < DEG_CAP ? d : DEG_CAP;
+        ds += x;
+        dq += x * x;
+    }
     for (int o = 32; o > 0; o >>= 1) {
         const uint32_t y = __shfl_xor(m, o);
         m = y > m ? y : m;
+        ds += __shfl_xor(ds, o);
+        dq += __shfl_xor(dq, o);
     }
-    if (lane_id() == 0)
+    __shared__ unsigned long long wg[3][CHECK_NT / WAVE];
+    if (lane_id() == 0) {
+        const int j = threadIdx.x / WAVE;
+        wg[0][j] = m;
+        wg[1][j] = ds;
+        wg[2][j] = dq;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int j = 1; j < CHECK_NT / WAVE; ++j) {
+            m = wg[0][j] > m ? (uint32_t)wg[0][j] : m;
+            ds += wg[1][j];
+            dq += wg[2][j];
+        }
         atomicMax(&sum->max_indeg, m);
+        atomicAdd(&sum->deg_sum, ds);
+        atomicAdd(&sum->deg_squares, dq);
+    }
 }
 
 // Sort keys of the renumbering: decreasing in-degree; the stable sort keeps
@@ -669,8 +697,8 @@ void create_graph_device(int32_t n, int64_t nnz64, const int64_t *row_ptr, const
                                                  CHECK_WGS)),
                        dim3(CHECK_NT), 0, st, n, nnz, row_ptr, col, w, indeg, dsum);
     hipLaunchKernelGGL(k_ingest_bad_values, dim3(1), dim3(1), 0, st, col, w, dsum);
-    hipLaunchKernelGGL(k_max_indeg, dim3((unsigned)blocks_for((size_t)n, 256, 256)), dim3(256), 0, st,
-                       indeg, n, dsum); // one atomic a wave: few waves
+    hipLaunchKernelGGL(k_degrees, dim3((unsigned)blocks_for((size_t)n, CHECK_NT, 256)),
+                       dim3(CHECK_NT), 0, st, indeg, row_ptr, n, dsum);
     hip_check(hipGetLastError(), "ingest check");
     IngestSummary S;
     hip_check(hipMemcpyAsync(&S, dsum, sizeof S, hipMemcpyDeviceToHost, st), "summary");
@@ -702,6 +730,7 @@ void create_graph_device(int32_t n, int64_t nnz64, const int64_t *row_ptr, const
     g->wbytes = wmax <= 255 ? 1 : (wmax <= 65535 ? 2 : 4);
     g->avg_deg = S.nz_rows ? (double)nnz64 / (double)S.nz_rows : 0.0;
     g->wmean = nnz ? (double)S.wsum / (double)nnz64 : 1.0;
+    g->deg_spread = spread_of((double)S.nz_rows, (double)S.deg_sum, (double)S.deg_squares);
 
     SortBufs tmp;
     const uint32_t *order = nullptr; // the renumbering, if any

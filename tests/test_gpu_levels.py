@@ -127,3 +127,39 @@ def test_hubs_that_improve_each_other(n, hub, threads):
         d, sg, _ = G.source_state(1, wg_threads=threads, wg_min_deg=hub, **opts)
         assert np.array_equal(d, od) and np.array_equal(sg, osg), opts
     G.close()
+
+
+def lattice(side: int, hub_arcs: int):
+    """A grid whose middle vertex has `hub_arcs` more arcs."""
+    i = np.arange(side * side).reshape(side, side)
+    c = int(i[side // 2, side // 2])
+    far = np.setdiff1d(np.arange(c - side // 3, c + side // 3), [c - 1, c, c + 1])[:hub_arcs]
+    u = np.concatenate([i[:, :-1].ravel(), i[:-1].ravel(), np.full(far.shape[0], c)])
+    v = np.concatenate([i[:, 1:].ravel(), i[1:].ravel(), far])
+    w = np.random.default_rng(side).integers(1, 256, u.shape[0])
+    return gg.undirected_from_edges(side * side, u, v, w)
+
+
+@pytest.mark.parametrize("side, hub_arcs", [(60, 6), (300, 6), (300, 60)])
+def test_one_wide_vertex_changes_no_plan(side, hub_arcs):
+    """A grid is handled as one whether or not a few of its vertices have more than 8
+    arcs: the same threads, no team, and nearly the same band width."""
+    torch = pytest.importorskip("torch")
+    plain, wide = lattice(side, 0), lattice(side, hub_arcs)
+    P, W = bc.Graph(plain), bc.Graph(wide)
+    rp, col, w = (torch.from_numpy(a).cuda() for a in (wide.row_ptr, wide.col, wide.w))
+    torch.cuda.synchronize()
+    D = bc.Graph.from_device(wide, rp, col, w, stream=torch.cuda.current_stream().cuda_stream)
+    for k in (1, 300, 600):
+        s = np.resize(np.array([0, side, plain.n - 1], np.int32), k)
+        (_, a), (got, b), (_, d) = (G.bc(s) for G in (P, W, D))
+        for f in ("wg_threads", "lds_vertices"):
+            assert a[f] == b[f] == d[f], (f, k)
+        assert b["lds_vertices"] > 0 and b["delta"] == d["delta"]
+        assert abs(a["delta"] - b["delta"]) <= 0.05 * a["delta"], k
+        want = sum(np.count_nonzero(s == v) * oracle.oracle_bc(wide, np.array([v]))
+                   for v in np.unique(s))
+        nz = want != 0
+        assert np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11
+    for G in (P, W, D):
+        G.close()
