@@ -582,10 +582,11 @@ static bool narrow_graph(const bc_graph *g)
 // / 64; R-MAT scale 14 15-31 / 32, 17 4-7 / 12, 20 2-4 / 5.  Against 4 maximum
 // weights over the average degree at any size: R-MAT scale 20, 256 sources 110 ->
 // 66 ms, Barabasi-Albert 100k, 1024 sources 37.3 -> 28.4, ER 500k, 256 sources 74 ->
-// 62.  Graphs of narrow frontiers and long paths (narrow_graph) want whole weights:
-// 32 x 32 grid 8 maximum weights, 100 x 100 2 to 4, 1000 x 1000 0.7 to 1.  A team pays a barrier over several workgroups per step
-// and wants wider bands (Barabasi-Albert 1M 100-200, R-MAT scale 20 7-15, ER 500k
-// 50).  The plain form, which launches every step, keeps the size-independent
+// 62.  But no wider than twice that, as the paths of dense graphs are short.
+// Graphs of narrow frontiers and long paths (narrow_graph) want whole weights:
+// 32 x 32 grid 8 maximum weights, 100 x 100 2 to 4, 1000 x 1000 0.7 to 1.  A team
+// pays a barrier over several workgroups per step and wants wider bands
+// (Barabasi-Albert 1M 100-200, R-MAT scale 20 7-15, ER 500k 50).  The plain form, which launches every step, keeps the size-independent
 // width.
 int default_delta(const bc_graph *g, int form, int team)
 {
@@ -598,6 +599,7 @@ int default_delta(const bc_graph *g, int form, int team)
     } else {
         d = (g->renumbered ? 0.2 : 0.5) * wmax *
             std::min(1.0, std::pow((double)g->nnz / 8e4, -0.45));
+        d = std::min(d, 8.0 * wmax / avg); // paths are short where degrees are high
         if (team > 1)
             d *= 5.0;
     }

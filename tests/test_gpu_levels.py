@@ -163,3 +163,20 @@ def test_one_wide_vertex_changes_no_plan(side, hub_arcs):
         assert np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11
     for G in (P, W, D):
         G.close()
+
+
+@pytest.mark.parametrize("n", [300, 700])
+def test_bands_of_dense_graphs(n):
+    """The bands of a dense graph are not much wider than its paths are long: eight
+    maximum weights over the degree at most, five times that for a team."""
+    a, b = np.triu_indices(n, 1)
+    g = gg.undirected_from_edges(n, a, b, np.random.default_rng(n).integers(1, 1001, a.shape[0]))
+    G = bc.Graph(g)
+    for k, team in ((n, 1), (64, 1), (1, 5)):
+        s = np.arange(k, dtype=np.int32)
+        got, st = G.bc(s)
+        assert 1 <= st["delta"] <= team * 8 * 1000 / (n - 1), (k, st["delta"])
+        want = oracle.oracle_bc(g, s)
+        nz = want != 0
+        assert np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11
+    G.close()
