@@ -616,12 +616,16 @@ int default_delta(const bc_graph *g, int form, int team)
 // sources 1.11 / 0.70 / 0.56, 4096 sources 12.6 / 10.3 / 9.0; Barabasi-Albert
 // 100k, 16 sources 15.3 / 8.8 / 5.5, 1024 sources 64 / 54 / 46.
 // Two exceptions: small graphs, whose frontiers do not fill 1024 threads (ER
-// 1000, 16 sources 0.25 / 0.22 / 0.22, all sources 0.49 / 0.56 / 0.80), and
-// graphs whose frontiers stay narrow at any size, grids and rings above all: more
-// sources than CUs then run side by side (100 x 100 grid, 1024 sources 3.3 / 4.5 /
-// 7.9, with one vertex of 10 arcs 3.4 / 5.3 / 9.1; 300 x 300 grid, 512 sources 17.5 /
-// 15.6 / 21.3; ring of 20,000 vertices of 10 arcs, 512 sources 29.8 / 28.6 / 49.3,
-// 1024 34.6 / 57 / 98).  Even degrees tell them (a ring with shortcuts counts as one,
+// 1000, 16 sources 0.25 / 0.22 / 0.22, all sources 0.49 / 0.56 / 0.80; up to 65536
+// arcs ER 3000 of 8 arcs a vertex, 1024 sources 0.71 / 0.72 / 0.96, 8000 of 4 1.58 /
+// 1.35 / 1.66, of 8 1.90 / 1.74 / 1.67; 8000 points of a plane with 6 arcs to those near
+// 3.39 / 5.16 / 9.14; beyond, ER 20,000 of 4 5.4 / 4.1 / 3.4; skewed graphs are faster
+// with 1024 before that, R-MAT scale 12, 320 sources 0.70 / 0.57 / 0.48), and graphs
+// whose frontiers stay narrow at any size, grids and rings above all: more sources
+// than CUs then run side by side (100 x 100 grid, 1024 sources 3.3 / 4.5 / 7.9, with
+// one vertex of 10 arcs 3.4 / 5.3 / 9.1; 300 x 300 grid, 512 sources 17.5 / 15.6 /
+// 21.3; ring of 20,000 vertices of 10 arcs, 512 sources 29.8 / 28.6 / 49.3, 1024
+// 34.6 / 57 / 98).  Even degrees tell them (a ring with shortcuts counts as one,
 // 100,000 vertices of 10 arcs, 512 sources 17.7 / 14.4 / 14.3) up to 32 arcs a
 // vertex; denser graphs fill their frontiers (complete, 2500 vertices, 600 sources
 // 24.3 / 23.8 / 22.4).
@@ -630,8 +634,10 @@ int default_wg_threads(const bc_graph *g, int64_t k)
     if (g->n <= 2048)
         return k <= g->num_cus / 4 ? 512 : 256;
     const bool even = g->deg_spread < 0.5 && g->avg_deg <= 32.0;
-    if (k <= g->num_cus || (g->maxdeg > 8 && !even))
+    if (k <= g->num_cus)
         return 1024;
+    if (g->maxdeg > 8 && !even)
+        return g->renumbered || g->nnz > 65536 ? 1024 : 512;
     return k <= 2 * (int64_t)g->num_cus ? 512 : 256;
 }
 

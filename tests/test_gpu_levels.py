@@ -180,3 +180,19 @@ def test_bands_of_dense_graphs(n):
         nz = want != 0
         assert np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11
     G.close()
+
+
+@pytest.mark.parametrize("n, threads", [(8192, 512), (8193, 1024)])
+def test_threads_of_small_random_graphs(n, threads):
+    """Random graphs of up to 65536 arcs with more sources than compute units."""
+    g = gg.er_graph(n, 4 * n, 1, 100, seed=n)
+    assert g.nnz == 8 * n
+    G = bc.Graph(g)
+    s = np.resize(np.array([0, 5, n - 1], np.int32), 300)
+    got, st = G.bc(s)
+    assert st["wg_threads"] == threads
+    assert G.bc(s[:256])[1]["wg_threads"] == 1024
+    want = 100 * oracle.oracle_bc(g, s[:3])
+    nz = want != 0
+    assert np.max(np.abs(got[nz] - want[nz]) / want[nz]) <= 1e-11
+    G.close()
