@@ -126,6 +126,8 @@ typedef struct {
     /* the autotuner's cached choice (bc_options.autotune); 0 fields before it ran */
     int32_t tuned;        /* 1 once a call with autotune set has tuned this graph */
     int32_t tuned_delta, tuned_wg_threads, tuned_lane_max_deg, tuned_dep_mode;
+    /* (of the degree thresholds only wg_min_deg is searched: the other two are those
+       that the tuning call ran with) */
     int32_t tuned_expand_lane_deg, tuned_wave_max_deg, tuned_wg_min_deg;
     int32_t tuned_batch;  /* sources in flight; 0 = the full occupancy of the workgroup size */
     int32_t tuned_lds_bits; /* width of the LDS distance entries */
@@ -138,7 +140,9 @@ bc_status bc_get_graph_info(const bc_graph *g, bc_graph_info *info);
 typedef enum {
     BC_MODE_AUTO = 0,    /* batched */
     BC_MODE_BATCHED = 1, /* many sources in flight, one workgroup and one state slab per source,
-                            one persistent launch (coarse-grained source parallelism, Sec. 3.1) */
+                            one persistent launch (coarse-grained source parallelism, Sec. 3.1);
+                            a few sources of a large graph, with the launch options left
+                            open, take several workgroups each */
     BC_MODE_PLAIN = 2,   /* one source at a time on the whole GPU, phase by phase */
     BC_MODE_INTERLEAVED = 3 /* sources in groups of 64 sharing one wavefront, one lane per
                                source, the state of a group laid out [vertex][source] so that
@@ -166,11 +170,11 @@ typedef struct {
                              by one lane, more by a whole 64-lane wave (plain form: in-arcs,
                              and out-arcs in the dependency pass) */
     int32_t wg_threads;   /* batched: threads per workgroup (256, 512 or 1024; 0 = by graph and
-                             number of sources); with batch set, a CU's LDS is shared only by the workgroups those
-                             sources need */
+                             number of sources); with batch set, a CU's LDS is shared only by
+                             the workgroups those sources need */
     int32_t autotune;     /* 1 = time candidate settings once per graph and keep the best:
                              band width, workgroup size, dependency method, lane_max_deg,
-                             the degree tiers and the sources in flight, each
+                             wg_min_deg, lds_bits and the sources in flight, each
                              unless set here, on a prefix of the source list (batched
                              form); later calls reuse the choice (bc_get_graph_info) */
     int32_t accumulate;   /* 0 = default, 1 = per-slot partial sums + reduction,
@@ -197,15 +201,17 @@ typedef struct {
                              vertices below the window and values beyond it are kept in
                              device memory.  Suits graphs whose arc weights are about the
                              window's width or less */
-    /* Degree tiers (the degree-aware thread mapping of Sec. 3.4 on 64-lane
-       wavefronts).  The adaptive frontier expansion (virtual_warp = 0) spreads
-       the arcs of a wave's queued vertices evenly over its lanes; in the batched
-       form a vertex with more than wg_min_deg out-arcs is expanded by the whole
-       workgroup after the pass.  The plain form's count pass hands vertices with
-       more than wave_max_deg in-arcs to a whole wave.  expand_lane_deg has no effect but
-       as the lower bound of wave_max_deg.  0 = default (8, 64, 512); a
-       threshold below the one before it is raised to it.  The plain form has no
-       workgroup tier; the interleaved form uses none of them. */
+    /* Degree thresholds (the degree-aware thread mapping of Sec. 3.4 on 64-lane
+       wavefronts).  The adaptive frontier expansion (virtual_warp = 0) spreads the
+       arcs of a wave's queued vertices evenly over its lanes, so that it has no
+       classes of vertices by degree but one: in the batched form a vertex with more
+       than wg_min_deg out-arcs is expanded by the whole workgroup after the pass.
+       The plain form's count pass hands vertices with more than wave_max_deg
+       in-arcs to a whole wave.  expand_lane_deg, and in the batched form
+       wave_max_deg, have no other effect than as lower bounds of the threshold after
+       them: one below the one before it is raised to it.  0 = default (8, 64, 512;
+       wg_min_deg 1024 where a source has several workgroups).  The plain form has no
+       workgroup threshold; the interleaved form uses none of them. */
     int32_t expand_lane_deg;
     int32_t wave_max_deg;
     int32_t wg_min_deg;

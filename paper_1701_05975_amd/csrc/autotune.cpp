@@ -44,7 +44,7 @@ struct Search {
     }
 };
 
-// Keeps the tier thresholds in order (lane <= group <= workgroup).
+// Keeps the degree thresholds in order (bc_options).
 void order_tiers(ResolvedOptions &t)
 {
     t.wave_deg = std::max(t.wave_deg, t.lane_deg);

@@ -199,7 +199,7 @@ void set_inarc_bound(bc_graph *g, hipStream_t st);
 // Far-bucket ring of a batched launch with band width r.delta: whether it is
 // used, and its number of buckets.
 void bucket_plan(const bc_graph *g, const ResolvedOptions &r, int &buckets, int &nbk);
-// Degree-tier fields of the batched kernel's arguments.
+// Hub fields of the batched kernel's arguments.
 void set_tier_args(const bc_graph *g, int wg_deg, BatchArgs &a);
 void read_device_counters(bc_graph *g, hipStream_t st, DevCounters &out);
 // Status of a finished computation from its device counters (throws on an

@@ -195,7 +195,7 @@ class HipExec {
         a.perm = g->perm_dev();
         a.H = c->lds_vertices;
         a.lds_bits = c->lds_bits;
-        set_tier_args(g, tier_for(g, 2), a);
+        set_tier_args(g, wg_deg_for(g), a);
         a.push = dep_mode_for(g) == 1 ? 1 : 0;
         a.ebc = nullptr;
         a.emap = nullptr;
@@ -320,19 +320,17 @@ class HipExec {
             return opts_.compute.lane_max_deg;
         return g->tuned.valid ? g->tuned.lane_max : 32;
     }
-    // degree tiers: 2 is the workgroup per hub
-    int tier_for(bc_graph *g, int which) const
+    // the expansion's workgroup threshold (the thresholds keep their order)
+    int wg_deg_for(bc_graph *g) const
     {
         const bc_options &o = opts_.compute;
-        const int given[3] = {o.expand_lane_deg, o.wave_max_deg, o.wg_min_deg};
-        const int tuned[3] = {g->tuned.lane_deg, g->tuned.wave_deg, g->tuned.wg_deg};
-        const int def[3] = {BC_DEF_LANE_DEG, BC_DEF_WAVE_DEG, BC_HUB_DEG};
-        int t[3];
-        for (int i = 0; i < 3; ++i)
-            t[i] = given[i] > 0 ? given[i] : (g->tuned.valid && tuned[i] > 0 ? tuned[i] : def[i]);
-        t[1] = std::max(t[1], t[0]);
-        t[2] = std::max(t[2], t[1]);
-        return t[which];
+        const auto &t = g->tuned;
+        auto pick = [&](int given, int tuned, int def) {
+            return given > 0 ? given : (t.valid && tuned > 0 ? tuned : def);
+        };
+        return std::max({pick(o.expand_lane_deg, t.lane_deg, BC_DEF_LANE_DEG),
+                         pick(o.wave_max_deg, t.wave_deg, BC_DEF_WAVE_DEG),
+                         pick(o.wg_min_deg, t.wg_deg, BC_HUB_DEG)});
     }
     int dep_mode_for(bc_graph *g) const
     {
