@@ -144,7 +144,7 @@ void autotune(bc_graph *g, ResolvedOptions &r, const bc_options *opt, const int3
             }
         }
         if (!o.wg_min_deg && g->maxdeg > 256 && !S.best.vw) {
-            // only graphs with vertices above the candidates have a workgroup tier
+            // only graphs with vertices above the candidates have hubs
             const int h0 = S.best.wg_deg;
             for (int hd : {256, 1024, 4096}) {
                 if (hd == h0 || hd < S.best.wave_deg || hd >= g->maxdeg)

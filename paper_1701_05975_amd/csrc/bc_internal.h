@@ -80,7 +80,7 @@ struct ResolvedOptions {
     int lds_vertices = 0; // H: distances kept in LDS per source
     int lds_bits = 32;    // width of an LDS distance entry (8, 16 or 32)
     int dep_mode = 1;     // 1 push along the recorded DAG, 2 pull over out-arcs
-    int vw = 0;           // expansion lanes per vertex (0 adaptive)
+    int vw = 0;           // expansion lanes per vertex (0: arcs laid out flat)
     int lane_deg = BC_DEF_LANE_DEG; // lower bound of wave_deg (reported only)
     int wave_deg = BC_DEF_WAVE_DEG; // plain form's counts: a wave above this many in-arcs
     int wg_deg = BC_HUB_DEG;        // expansion: the whole workgroup above this (batched form)

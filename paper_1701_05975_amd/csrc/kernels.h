@@ -23,7 +23,7 @@ struct BatchArgs {
     int32_t lds_bits;             // width of the LDS distance entries: 32, 16 or 8 (8: packed arcs)
     int32_t hubs;                 // the graph has vertices of more than wg_deg arcs
     int32_t push;                 // 1: dependencies along the recorded DAG; 0: pulls over out-arcs
-    int32_t vw;                   // expansion: 0 adaptive lane/wave, else lanes per vertex
+    int32_t vw;                   // expansion: 0 arcs laid out flat, else lanes per vertex
     int32_t narrow = 0;           // expansion of short queues by small groups (NARROW_DEG)
     int32_t node_parallel;        // expansion scans every vertex instead of the queue
     double *ebc;                  // optional edge betweenness output (caller arc order)
@@ -72,7 +72,7 @@ struct PlainCtl {
     long long src_idx;
     int near_len, next_cnt, order_cnt, far_cnt, kept_cnt, pend_len, pend_cnt;
     int cur, fcur, pcur;
-    int32_t gen, band_gen;
+    int32_t gen;
     uint32_t thr, thr_old, far_min;
     int band_start, nbands, dband, round, b0, b1;
     unsigned long long iters, iter_cap;

@@ -35,7 +35,7 @@ struct WgCtl {
     int outer_cnt, okept_cnt, resplit;
     int32_t huge_q[EXPAND_WG_CAP]; // hubs of the current pass, expanded by the workgroup
     int cur, fcur, ocur;
-    int32_t gen, band_gen;
+    int32_t gen;
     uint32_t thr, thr_old, far_min, bound, bound_old, outer_min;
     int32_t lvl, lvl_base; // count rounds over the slab's life, and at the source's start
     int band_start, nbands, nlev;
@@ -120,7 +120,6 @@ __device__ __forceinline__ bool bucket_next_band(const Slab &S, WgCtl &C, const 
             C.bound_old = C.bound;
             C.bound = sat_add_u32(0u, (b + (uint64_t)nbk) * D);
             C.gen += 1;
-            C.band_gen = C.gen;
             C.near_len = 0;
             C.resplit = C.outer_cnt > 0 &&
                         (C.forced || (uint64_t)(C.outer_min / D) < b + (uint64_t)nbk);
@@ -470,7 +469,6 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             C.far_cnt = 0;
             C.outer_cnt = 0;
             C.ocur = 0;
-            C.band_gen = C.gen;
             C.thr = a.delta;
             C.far_min = BC_INF;
             C.outer_min = BC_INF;
@@ -515,7 +513,6 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
             ec.nworkers = NT / WAVE;
             ec.marks = C.marks[ec.worker];
             ec.thr = (uint32_t)__builtin_amdgcn_readfirstlane((int)C.thr);
-            ec.band_gen = C.band_gen;
             ec.order = S.order;
             ec.order_cnt = &C.order_cnt;
             ec.far_q = C.fcur ? S.fb : S.fa;
@@ -633,7 +630,6 @@ __global__ __launch_bounds__(NT, 4) void k_batched(BatchArgs a)
                 C.thr = sat_add_u32(lo, (uint64_t)a.delta);
                 C.far_min = BC_INF;
                 C.gen += 1;
-                C.band_gen = C.gen;
                 C.near_len = 0;
                 C.kept_cnt = 0;
                 C.okept_cnt = 0;
@@ -880,7 +876,6 @@ __device__ void plain_end_band(PlainCtl *c, const Slab &S, uint32_t delta)
     c->thr = t > BC_INF ? BC_INF : (uint32_t)t;
     c->far_min = BC_INF;
     c->gen += 1;
-    c->band_gen = c->gen;
     c->near_len = 0;
     c->kept_cnt = 0;
     c->iters += 1;
@@ -920,7 +915,6 @@ __global__ void k_plain_setup(PlainArgs a, int32_t s, long long idx, double *bc_
     c->kept_cnt = 0;
     c->pend_cnt = 0;
     c->pend_len = 0;
-    c->band_gen = c->gen;
     c->thr = a.delta;
     c->thr_old = 0;
     c->far_min = BC_INF;
@@ -972,7 +966,6 @@ __global__ __launch_bounds__(256) void k_plain_step(PlainArgs a)
         ec.nworkers = nworkers;
         ec.thr = c->thr;
         ec.tag_next = c->gen + 1;
-        ec.band_gen = c->band_gen;
         ec.next_q = c->cur ? S.qa : S.qb;
         ec.next_cnt = &c->next_cnt;
         ec.order = S.order;

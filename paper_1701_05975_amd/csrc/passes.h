@@ -158,12 +158,11 @@ struct ExpandCtx {
     int len;
     int all_vertices;     // node-parallel: scan every vertex, expand those queued now
     int32_t cur_tag;      // tag of the queue being expanded (node-parallel filter)
-    int vw;               // 0: lane or wave by degree; else a fixed group of vw lanes
+    int vw;               // 0: arcs laid out flat; else a fixed group of vw lanes per vertex
     int worker, nworkers; // wave index and wave count over the item list
     uint32_t *marks;      // 2 EXPAND_UNROLL words of LDS of this wave (flat_starts)
     uint32_t thr;         // band threshold: d < thr is near
     int32_t tag_next;     // tag of the queue being filled
-    int32_t band_gen;     // tag of the band's first queue
     int32_t *next_q;
     int *next_cnt;
     int32_t *order;
@@ -173,11 +172,11 @@ struct ExpandCtx {
     uint32_t bound;       // far values at or above go to the outer pile (BC_INF: none)
     int32_t *outer_q;
     int *outer_cnt;
-    int32_t *huge_q;      // optional: vertices with more than EXPAND_WG_DEG arcs are listed
-    int *huge_cnt;        // here for the whole workgroup to expand after the pass
+    int32_t *huge_q;      // optional: vertices with more than wg_deg arcs are listed here
+    int *huge_cnt;        // for the whole workgroup or team to expand after the pass
     int keys;             // record each vertex's (distance, predecessor) key and ties
     const uint32_t *trow; // with keys: in-row offsets, whose slices hold the tie entries
-    uint32_t wg_deg;      // more arcs than this (batched, huge_q set): the whole workgroup
+    uint32_t wg_deg;
     // Far-bucket ring (batched form, relax<.., true>; else the two-tier pile above).  A far
     // value below `bound` goes to bucket value / bdelta, slot bucket % nbk,
     // when the value it replaces lay in a higher bucket (or beyond the ring);

@@ -6,10 +6,9 @@
 
 #define BC_INF 0x7fffffffu
 #define WAVE 64
-// Default degree thresholds of the adaptive mapping: at most BC_DEF_LANE_DEG
-// arcs -> one lane, at most BC_DEF_WAVE_DEG -> a group of lanes, more -> a
-// wave; in the batched expansion more than BC_HUB_DEG -> the whole workgroup
-// (only graphs that have such a vertex pay for the step).
+// Default degree thresholds (bc_options): more than BC_DEF_WAVE_DEG in-arcs take a
+// wave in the plain form's counts; in the batched expansion more than BC_HUB_DEG
+// arcs -> the whole workgroup (only graphs that have such a vertex pay for the step).
 #define BC_DEF_LANE_DEG 8
 #define BC_DEF_WAVE_DEG 64
 #define BC_HUB_DEG 512

@@ -267,7 +267,6 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
                 ec.marks = marks;
                 ec.thr = thr;
                 ec.tag_next = gen + 1;
-                ec.band_gen = 0;
                 ec.next_q = cur ? S.qa : S.qb;
                 ec.next_cnt = &c->step[y.interval][TEAM_NEAR];
                 ec.order = S.order + total;
