@@ -62,7 +62,6 @@ struct TeamSync {
     unsigned int epoch; // arrivals that complete the next barrier (thread 0)
     int interval;       // barrier intervals so far, mod 3
     unsigned int looks; // looks at a barrier before it has failed
-    unsigned long long *err;
 };
 
 // Barrier of the team.  The release before and the acquire after it (of thread
@@ -72,8 +71,8 @@ struct TeamSync {
 // ends; the bound is there for the case that this is not so.  It counts looks,
 // not time: on a GPU shared with other processes a team is slow while it is off
 // the GPU, and then all of it is.  A member that sees a failure, its own or
-// another's, says so itself: the first member may be the one that came late and
-// sees its barriers complete, and its next one can be that of a new source.
+// another's, reports it itself at the end: the first member may be the one that came
+// late and sees its barriers complete, and its next one can be that of a new source.
 // `par`, `band`: which of the source and far pile words to read.
 __device__ __forceinline__ bool team_barrier(TeamWg &W, TeamSync &y, int par, int band)
 {
@@ -95,8 +94,10 @@ __device__ __forceinline__ bool team_barrier(TeamWg &W, TeamSync &y, int par, in
             const bool late = ++looks >= y.looks;
             if (late)
                 ag_store(&c->failed, 1u);
-            if (late || ((looks & 1023u) == 0u && ag_load(&c->failed)))
+            if ((late || (looks & 1023u) == 0u) && ag_load(&c->failed)) {
+                W.failed = 1;
                 break;
+            }
         }
         __threadfence();
         for (int i = 0; i < TEAM_STEP_WORDS; ++i)
@@ -104,10 +105,6 @@ __device__ __forceinline__ bool team_barrier(TeamWg &W, TeamSync &y, int par, in
         W.far_cnt = ag_load(&c->far_cnt[band]);
         W.far_min = ag_load(&c->far_min[band]);
         W.src = ag_load(&c->src[par]);
-        if (ag_load(&c->failed)) {
-            W.failed = 1;
-            atomicOr(y.err, (unsigned long long)BC_ERRBIT_INTERNAL);
-        }
     }
     y.interval = y.interval == 2 ? 0 : y.interval + 1;
     __syncthreads();
@@ -122,7 +119,7 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
     const int tid = threadIdx.x;
     const DevGraph &g = a.g;
     const int n = g.n;
-    TeamSync y{nullptr, 0u, 0, ta.looks, a.err};
+    TeamSync y{nullptr, 0u, 0, ta.looks};
     if (tid == 0) {
         W.failed = 0;
         W.team = -1;
@@ -466,10 +463,13 @@ __global__ __launch_bounds__(TEAM_THREADS, 4) void k_team(TeamArgs ta)
     flush(st_arcs, &a.stats->arcs);
     flush(st_dag, &a.stats->dag);
     flush(st_imp, &a.stats->improvements);
+    if (threadIdx.x == 0 && W.failed)
+        atomicOr(&a.err[0], (unsigned long long)BC_ERRBIT_INTERNAL);
     if (lead) {
-        // (after a failed barrier another member can be a round further on)
-        S.hdr[0] = gen + W.failed;
-        S.hdr[1] = lvl + W.failed;
+        S.hdr[0] = gen;
+        // after a failed barrier another member can be a round further on: the next
+        // source clears the numbers
+        S.hdr[1] = W.failed ? (1 << 30) + 1 : lvl;
         atomicAdd(&a.stats->sigma_rounds, srounds);
         atomicAdd(&a.stats->delta_rounds, drounds);
         for (int i = 0; i < 5; ++i)
