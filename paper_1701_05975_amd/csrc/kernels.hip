@@ -35,21 +35,22 @@ struct WgCtl {
     int outer_cnt, okept_cnt, resplit;
     int32_t huge_q[EXPAND_WG_CAP]; // hubs of the current pass, expanded by the workgroup
     int cur, fcur, ocur;
-    int abort; // (further down, 4 to 10 VGPRs of k_batched spill instead of 0 to 4)
-    int32_t gen;
+    // (bcur, the bucket of the ring's current band: with it further down, 4 to 10 VGPRs of
+    // k_batched spill instead of 0 to 4)
+    int32_t gen, bcur;
     uint32_t thr, thr_old, far_min, bound, bound_old, outer_min;
     int32_t lvl, lvl_base; // count rounds over the slab's life, and at the source's start
     int band_start, nbands, nlev;
+    int abort;
     int32_t prev_s; // this slab's previous source whose dependencies are not added yet
     double *prev_bc; // and the output they go to (atomic accumulation)
     long long src_idx;
     unsigned long long iters;
     unsigned int bands, srounds, drounds;
     unsigned long long ticks[5]; // per-phase device time of this workgroup
-    // far-bucket ring: entries per slot, the bucket of the current band, the
-    // next non-empty one (offset from bcur, 0 = none), outer pile must be scanned
+    // far-bucket ring: entries per slot, the next non-empty bucket (offset from bcur,
+    // 0 = none), outer pile must be scanned
     int bcnt[BC_BUCKETS_MAX];
-    int32_t bcur;
     int bnext, forced, overflowed; // overflowed: a bucket was full in this source
 };
 
