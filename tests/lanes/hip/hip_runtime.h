@@ -4,9 +4,10 @@
 //
 // A workgroup is a host thread, each of its work-items a fiber of that thread.  A
 // wave's fibers meet at every cross-lane operation and a workgroup's at every
-// barrier; in between, and at one atomic in eight, the scheduler goes on with a
-// wave chosen at random, so that a seed is an interleaving.  Cross-lane operations
-// have to be reached by all 64 lanes (checked).  Memory is sequentially consistent.
+// barrier; there, after one atomic in eight and at wave barriers, which hold the
+// lanes that reach them, the scheduler goes on with a wave chosen at random, so that a
+// seed is an interleaving.  Cross-lane operations have to be reached by all 64 lanes
+// (checked).  Memory is sequentially consistent.
 #pragma once
 
 #include <setjmp.h>
@@ -103,14 +104,13 @@ __attribute__((noinline)) inline void yield()
 
 inline void meet(Meet &m)
 {
-    if (++m.here == m.n) {
-        m.here = 0;
-        ++m.epoch;
-        return;
-    }
     Lane *l = group->cur;
     l->waits = &m;
     l->epoch = m.epoch;
+    if (++m.here == m.n) {
+        m.here = 0;
+        ++m.epoch; // all go on in the wave's next turn
+    }
     yield();
 }
 
@@ -235,12 +235,12 @@ inline void launch(std::function<void()> kernel, dim3 grid, dim3 block)
 
 template <class T, class F> T update(T *p, F f) // atomic; the old value
 {
-    shuffle_waves();
     T was, now;
     __atomic_load(p, &was, __ATOMIC_SEQ_CST);
     do {
         now = f(was);
     } while (!__atomic_compare_exchange(p, &was, &now, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST));
+    shuffle_waves();
     return was;
 }
 
@@ -349,7 +349,7 @@ inline uint32_t __builtin_amdgcn_mbcnt_hi(uint32_t m, uint32_t add)
     const int l = lanes::lane();
     return add + (l <= 32 ? 0u : (uint32_t)__builtin_popcount(m & ((1u << (l - 32)) - 1u)));
 }
-inline void __builtin_amdgcn_wave_barrier() { lanes::collect(6, 0); }
+inline void __builtin_amdgcn_wave_barrier() { lanes::yield(); }
 inline void __builtin_amdgcn_fence(int, const char *) {}
 inline void __builtin_amdgcn_s_waitcnt(int) {}
 inline void __builtin_amdgcn_s_sleep(int)
