@@ -380,8 +380,9 @@ __device__ __forceinline__ void expand_pass_vw(const DevGraph &g, const Slab &S,
                 qbit_clear(S, (uint32_t)v);
             // no lane of the group reads the distance before its first lane has cleared
             // the bit: an improvement between the two would leave that lane with the old
-            // value (in this branch it costs nothing, behind it 1.4% on small grids)
-            __builtin_amdgcn_wave_barrier();
+            // value (a fence of the wave costs nothing; a wave barrier behind this branch
+            // cost small grids 1.4%)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             dv = dist_get(S, v);
         }
         for (uint32_t e = beg + sub; __ballot(e < end); e += W) { // the whole wave together

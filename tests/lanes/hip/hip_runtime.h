@@ -4,10 +4,11 @@
 //
 // A workgroup is a host thread, each of its work-items a fiber of that thread.  A
 // wave's fibers meet at every cross-lane operation and a workgroup's at every
-// barrier; there, after one atomic in eight and at wave barriers, which hold the
-// lanes that reach them, the scheduler goes on with a wave chosen at random, so that a
-// seed is an interleaving.  Cross-lane operations have to be reached by all 64 lanes
-// (checked).  Memory is sequentially consistent.
+// barrier; there, after one atomic in eight and at a wave's fences, the scheduler goes
+// on with a wave chosen at random, so that a seed is an interleaving.  Cross-lane
+// operations and wave barriers have to be reached by all 64 lanes (checked); a fence
+// holds those that reach it until the wave's next turn.  Memory is sequentially
+// consistent.
 #pragma once
 
 #include <setjmp.h>
@@ -109,7 +110,7 @@ inline void meet(Meet &m)
     l->epoch = m.epoch;
     if (++m.here == m.n) {
         m.here = 0;
-        ++m.epoch; // all go on in the wave's next turn
+        ++m.epoch; // the lanes after this one go on in this turn, the others in the next
     }
     yield();
 }
@@ -349,8 +350,8 @@ inline uint32_t __builtin_amdgcn_mbcnt_hi(uint32_t m, uint32_t add)
     const int l = lanes::lane();
     return add + (l <= 32 ? 0u : (uint32_t)__builtin_popcount(m & ((1u << (l - 32)) - 1u)));
 }
-inline void __builtin_amdgcn_wave_barrier() { lanes::yield(); }
-inline void __builtin_amdgcn_fence(int, const char *) {}
+inline void __builtin_amdgcn_wave_barrier() { lanes::collect(6, 0); }
+inline void __builtin_amdgcn_fence(int, const char *) { lanes::yield(); }
 inline void __builtin_amdgcn_s_waitcnt(int) {}
 inline void __builtin_amdgcn_s_sleep(int)
 {
